@@ -218,7 +218,9 @@ const char* ld_last_error(void);
  * ld_autotune): per union column its index and 4 FP64 values (plus 4 FP32
  * ones with LD_VT_FP32), 36 or 52 bytes, built on the device here when
  * groups of 4 rows hold at least 2 entries per union column (so at most
- * 18 or 26 bytes per entry).
+ * 18 or 26 bytes per entry), and tiles of 16 groups (2 bytes per union
+ * column, 4 per column of a tile's union and 2 per row group: 2 bytes per
+ * entry or less).
  * lambda_lo_hint / lambda_hi_hint > 0 replace the Gershgorin bounds
  * (Section 2.1); a Gershgorin lower bound <= 0 without a hint is replaced by
  * 1e-6 * lambda_hi.  n and nnz must fit int32. */
@@ -306,7 +308,10 @@ ld_status ld_request_bytes(ld_matrix* a, const ld_params* p, uint64_t* bytes);
  * default on such matrices for blocks of 16 columns or more where values
  * and vectors have the same type, with one chunk per lane for FP32 and two
  * for FP64, and ld_autotune tries it in every plain geometry of at most 2
- * chunks per lane.  A row's sum sees its
+ * chunks per lane.  Blocks of 16 columns or more take the row groups in tiles
+ * of 16 whose probe rows are gathered once into LDS, where every tile's union
+ * of columns fits; the lanes and chunks then do not change the product, and
+ * ld_autotune tries it in both chunk mappings.  A row's sum sees its
  * nonzero terms in CSR order, so the product's output is the CSR product's.
  * The groups are built on the device when the matrix is created.
  * ld_autotune times every such (L, C, E) with L a power of two and at most

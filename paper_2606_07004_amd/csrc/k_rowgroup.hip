@@ -12,7 +12,10 @@
 // ratio of entries to union columns.  A row's sum sees its own nonzero terms
 // in CSR order (a zero value adds an exact zero), so W is the CSR product's
 // W; the epilogue (scaling, early subtraction, store, fused inner products)
-// is the CSR product's, per row.
+// is the CSR product's, per row.  Blocks of 16 columns or more on matrices
+// whose tiles of 16 groups fit a block's LDS take the row-tile product
+// (k_rowtile.hip) instead: this one serves narrower blocks (its gathers are
+// short there and a 128-byte panel would idle) and matrices of very long rows.
 #include <climits>
 #include <type_traits>
 

@@ -1252,12 +1252,14 @@ hipError_t launch_spmm_batch(hipStream_t st, SpmmItem* items, int count) {
   for (int a = 0; a < count; ++a)
     if (!spmm_item_ok(items[a])) return hipErrorInvalidValue;
   auto key = [](const SpmmItem& it) -> uint64_t {
-    return (uint64_t)it.g.xbytes | ((uint64_t)it.vt << 8) | ((uint64_t)it.g.C << 16) |
+    const int tk = spmm_tile_key(it);  // a tile item's lanes and chunks are its own
+    return (uint64_t)it.g.xbytes | ((uint64_t)it.vt << 8) | ((uint64_t)(tk ? 0 : it.g.C) << 16) |
            ((uint64_t)it.nf << 24) | ((uint64_t)(it.g.lges > 0) << 32) |
-           ((uint64_t)it.g.rg << 33);
+           ((uint64_t)it.g.rg << 33) | ((uint64_t)tk << 40);
   };
   return launch_grouped(items, count, key, [&](const int* idx, int cnt) -> hipError_t {
     const SpmmItem& it = items[idx[0]];
+    if (spmm_tile_key(it)) return launch_spmm_tile_group(st, items, idx, cnt);
     if (it.g.rg) return launch_spmm_rg_group(st, items, idx, cnt);
     if (it.g.xbytes == 8) {
       if (it.vt == VT_F64) return spmm_launch_typed<double, double>(st, it.g.C, it.nf, items, idx, cnt);

@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include "ld_device.h"
+#include "row_tiles.h"
 
 namespace ld {
 
@@ -62,13 +63,29 @@ bool geom_usable(const Geom& g);
 // val[kRowGroup u + r] of row r (zero where the row has no entry there).
 // One gather of a neighbour's probe row then serves every row of the group
 // that references it; the rows' sums see their nonzero terms in CSR order.
-constexpr int kRowGroup = 4;
+
+struct RowTiles {
+  const int* tcol = nullptr;       // [ntile][ust] sorted union columns of each tile (the last repeated)
+  const int* tcnt = nullptr;       // [ntile] their number
+  const uint16_t* lidx = nullptr;  // per group entry: its column's index in the tile's union
+  const uint16_t* self = nullptr;  // per group: its first row's index in the tile's union
+  int ust = 0, umax = 0;           // umax: the largest tcnt; ust a multiple of kTileLoadRows
+  TileShape shape;
+};
 struct RowGroups {
   const int* gp = nullptr;
   const int* col = nullptr;
   const float* val = nullptr;    // FP32 values (FP32 probe blocks)
   const double* val64 = nullptr;  // FP64 values (FP64 probe blocks)
+  RowTiles tile;                  // tcol null: none
 };
+constexpr int kTileMinCols = 16;  // narrowest block of the row-tile product
+// Union size of each tile (tcnt, -1 when its groups hold too many columns),
+// then, with ust at least the largest, the tiles themselves.
+hipError_t launch_tile_count(hipStream_t st, int64_t n, const TileShape& s, const int* gp,
+                             const int* col, int* tcnt);
+hipError_t launch_tile_fill(hipStream_t st, int64_t n, const TileShape& s, const int* gp,
+                            const int* col, int ust, int* tcol, uint16_t* lidx, uint16_t* self);
 
 // Row groups of an n-row CSR matrix (rows sorted) on the device: cnt[g] =
 // group g's union columns; then, with gp the exclusive prefix sums of cnt
@@ -291,6 +308,11 @@ hipError_t launch_spmm_batch(hipStream_t st, SpmmItem* items, int count);
 // The row-group items of a batch (g.rg, checked by launch_spmm_batch), at
 // most kMaxBatch of them with the same C and nf: one launch.
 hipError_t launch_spmm_rg_group(hipStream_t st, SpmmItem* items, const int* idx, int cnt);
+// Non-zero where a row-group item takes the row-tile product (its matrix
+// keeps tiles and the block has at least 16 columns): items of one launch
+// share the key.
+int spmm_tile_key(const SpmmItem& it);
+hipError_t launch_spmm_tile_group(hipStream_t st, SpmmItem* items, const int* idx, int cnt);
 // Grid of a streaming kernel `fn` over g's rows (row groups with g.rg): at
 // most one resident wave of blocks, a multiple of 8 from 8 blocks up.
 int stream_grid(const Geom& g, const void* fn);

@@ -450,6 +450,15 @@ RowGroups Run::row_groups() const {
   r.col = a_->rg_col;
   r.val = a_->rg_val;
   r.val64 = a_->rg_val64;
+  if (a_->tl_col) {
+    r.tile.tcol = a_->tl_col;
+    r.tile.tcnt = a_->tl_cnt;
+    r.tile.lidx = a_->tl_idx;
+    r.tile.self = a_->tl_idx + a_->rg_nu + kTilePad;
+    r.tile.ust = a_->tl_ust;
+    r.tile.umax = a_->tl_umax;
+    r.tile.shape = a_->tl_shape;
+  }
   return r;
 }
 
@@ -1512,7 +1521,10 @@ ld_status Run::tune(hipStream_t st, int reps, ld_tune_result* out) {
       const size_t base = cand.size();
       const int ncolv = ld / (16 / xb_);
       if (ncolv <= 64) cand.push_back({ncolv | (1 << 13), 1});
-      for (size_t i = 0; i < base; ++i) {
+      if (a_->tl_col && ld >= kTileMinCols) {
+        // the row-tile product sets its own lanes: the other chunk mapping only
+        if (ncolv <= 64) cand.push_back({ncolv | (1 << 12) | (1 << 13), 1});
+      } else for (size_t i = 0; i < base; ++i) {
         const Geom g = candidate_geom(n_, ld, xb_, cand[i]);
         if (g.lges == 0 && g.ts == 0 && g.C <= 2 && !(g.L == ncolv && g.C == 1 && g.xil == 0))
           cand.push_back({cand[i].first | (1 << 13), cand[i].second});
@@ -2000,6 +2012,101 @@ static int64_t group_union_size(const int32_t* rp, const int32_t* ci, int64_t n,
   return cnt;
 }
 
+// Distinct columns of a sample of tiles of the given shape, per tile.
+static double sampled_tile_union(int64_t n, const int32_t* rp, const int32_t* ci,
+                                 const TileShape& s) {
+  const int64_t ng = (n + kRowGroup - 1) / kRowGroup;
+  const int ns = (int)std::min<int64_t>(s.ntile, 8);
+  std::vector<int32_t> cols;
+  int64_t total = 0;
+  for (int i = 0; i < ns; ++i) {
+    cols.clear();
+    const int64_t tile = (2 * i + 1) * s.ntile / (2 * ns);
+    for (int k = 0; k < kTileGroups; ++k) {
+      const int64_t g = tile_group(s, ng, tile, k);
+      if (g < 0) continue;
+      const int64_t r0 = g * kRowGroup, r1 = std::min(n, r0 + kRowGroup);
+      cols.insert(cols.end(), ci + rp[r0], ci + rp[r1]);
+    }
+    std::sort(cols.begin(), cols.end());
+    total += std::unique(cols.begin(), cols.end()) - cols.begin();
+  }
+  return ns > 0 ? (double)total / ns : 0.0;
+}
+
+// The tile shape: consecutive groups, or (a grid's rows in natural order) 4
+// groups on each of 4 lines where a sample of tiles then has a smaller union.
+// The line stride is the offset from a middle row to the centre of its next
+// run of consecutive columns.
+static TileShape choose_tile_shape(int64_t n, const int32_t* rp, const int32_t* ci) {
+  TileShape best = make_tile_shape(n, 0, 0);
+  const int64_t row = n / 2;
+  int32_t k = rp[row];
+  const int32_t end = rp[row + 1];
+  while (k < end && ci[k] <= row) ++k;
+  while (k < end && ci[k] == ci[k - 1] + 1) ++k;  // the diagonal's run (the diagonal is present)
+  if (k < end) {
+    int32_t q = k;
+    while (q + 1 < end && ci[q + 1] == ci[q] + 1) ++q;
+    const int64_t stride = ((int64_t)ci[k] + ci[q]) / 2 - row;
+    const int64_t sg = (stride + kRowGroup / 2) / kRowGroup;
+    if (sg >= 4) {
+      const TileShape s = make_tile_shape(n, sg, 4);
+      if (s.sg > 0 &&
+          sampled_tile_union(n, rp, ci, s) < sampled_tile_union(n, rp, ci, best))
+        best = s;
+    }
+  }
+  return best;
+}
+
+// No memory for the tiles: the matrix goes on without them (the groups then
+// gather for themselves).
+static hipError_t drop_tiles(ld_matrix* m) {
+  (void)hipGetLastError();
+  if (m->tl_cnt) (void)hipFree(m->tl_cnt);
+  if (m->tl_idx) (void)hipFree(m->tl_idx);
+  if (m->tl_col) (void)hipFree(m->tl_col);
+  m->tl_cnt = nullptr;
+  m->tl_idx = nullptr;
+  m->tl_col = nullptr;
+  return hipSuccess;
+}
+
+// Tiles of the matrix's row groups on the device; kept where every tile's
+// union fits the LDS of a block.
+static hipError_t build_tiles(hipStream_t st, ld_matrix* m, const TileShape& s) {
+  const int64_t ng = (m->n + kRowGroup - 1) / kRowGroup;
+  std::vector<int32_t> cnt((size_t)s.ntile);
+  hipError_t e = hipMalloc(&m->tl_cnt, (size_t)s.ntile * 4);
+  if (e == hipErrorOutOfMemory) return drop_tiles(m);
+  if (e == hipSuccess) e = launch_tile_count(st, m->n, s, m->rg_gp, m->rg_col, m->tl_cnt);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(cnt.data(), m->tl_cnt, cnt.size() * 4, hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess) e = hipStreamSynchronize(st);
+  if (e != hipSuccess) return e;
+  int ust = 0;
+  for (int32_t c : cnt) {
+    if (c < 1 || c > kTileMaxUnion) return hipSuccess;  // no tiles (the count buffer stays)
+    ust = std::max(ust, c);
+  }
+  const int umax = ust;
+  ust = (ust + kTileLoadRows - 1) / kTileLoadRows * kTileLoadRows;
+  e = hipMalloc(&m->tl_idx, ((size_t)m->rg_nu + kTilePad + (size_t)ng) * 2);
+  if (e == hipSuccess) e = hipMalloc(&m->tl_col, (size_t)s.ntile * ust * 4);
+  if (e == hipErrorOutOfMemory) return drop_tiles(m);
+  if (e == hipSuccess)
+    e = launch_tile_fill(st, m->n, s, m->rg_gp, m->rg_col, ust, m->tl_col, m->tl_idx,
+                         m->tl_idx + m->rg_nu + kTilePad);
+  if (e == hipSuccess) {
+    m->tl_ust = ust;
+    m->tl_umax = umax;
+    m->tl_shape = s;
+    m->bytes += (size_t)s.ntile * (4 + (size_t)ust * 4) + ((size_t)m->rg_nu + (size_t)ng) * 2;
+  }
+  return e;
+}
+
 ld_status ld_create_csr(ld_ctx* ctx, int64_t n, int64_t nnz, const int32_t* row_ptr,
                         const int32_t* col_idx, const double* values, int32_t vt,
                         double lambda_lo_hint, double lambda_hi_hint, ld_matrix** out) {
@@ -2074,6 +2181,9 @@ ld_status ld_create_csr(ld_ctx* ctx, int64_t n, int64_t nnz, const int32_t* row_
     if (m->rg_val) (void)hipFree(m->rg_val);
     if (m->rg_val64) (void)hipFree(m->rg_val64);
     if (m->rg_unused) (void)hipFree(m->rg_unused);
+    if (m->tl_col) (void)hipFree(m->tl_col);
+    if (m->tl_cnt) (void)hipFree(m->tl_cnt);
+    if (m->tl_idx) (void)hipFree(m->tl_idx);
   };
   hipError_t e = hipMalloc(&m->rp, (size_t)(n + 1) * 4);
   if (e == hipSuccess) e = hipMalloc(&m->ci, (size_t)nnz * 4);
@@ -2173,16 +2283,18 @@ ld_status ld_create_csr(ld_ctx* ctx, int64_t n, int64_t nnz, const int32_t* row_
         // FP32 values only with FP32 storage (mixed runs read them); FP64
         // values always (FP64 runs, and mixed runs on FP64 storage)
         const bool f32 = m->vt_lo == VT_F32;
-        if (e == hipSuccess && f32) e = hipMalloc(&m->rg_val, (size_t)nu * kRowGroup * 4);
-        if (e == hipSuccess) e = hipMalloc(&m->rg_val64, (size_t)nu * kRowGroup * 8);
+        if (e == hipSuccess && f32)
+          e = hipMalloc(&m->rg_val, ((size_t)nu + kTilePad) * kRowGroup * 4);
+        if (e == hipSuccess) e = hipMalloc(&m->rg_val64, ((size_t)nu + kTilePad) * kRowGroup * 8);
         if (e == hipSuccess)
           e = launch_rowgroup_fill(ctx->stream, n, m->rp, m->ci, m->v64, m->rg_gp, m->rg_col,
                                    m->rg_val, m->rg_val64);
-        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
         if (e == hipSuccess) {
           m->rg_nu = nu;
           m->bytes += ((size_t)ng + 1) * 4 + (size_t)nu * (4 + (f32 ? 12 : 8) * kRowGroup);
+          e = build_tiles(ctx->stream, m.get(), choose_tile_shape(n, row_ptr, col_idx));
         }
+        if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
       } else if (e == hipSuccess) {
         // the full count missed the ratio the sample promised: no groups (the
         // count buffer stays with the matrix, since a free would synchronise
@@ -2246,6 +2358,9 @@ ld_status ld_destroy(ld_matrix* a) {
   if (a->rg_val) (void)hipFree(a->rg_val);
   if (a->rg_val64) (void)hipFree(a->rg_val64);
   if (a->rg_unused) (void)hipFree(a->rg_unused);
+  if (a->tl_col) (void)hipFree(a->tl_col);
+  if (a->tl_cnt) (void)hipFree(a->tl_cnt);
+  if (a->tl_idx) (void)hipFree(a->tl_idx);
   a->ctx->n_matrices.fetch_sub(1);
   delete a;
   return LD_OK;

@@ -166,6 +166,12 @@ struct ld_matrix {
   double* rg_val64 = nullptr;
   int64_t rg_nu = 0;
   int* rg_unused = nullptr;  // a count buffer whose groups were not kept
+  // tiles of the row groups (null: none, the groups gather for themselves)
+  int* tl_col = nullptr;
+  int* tl_cnt = nullptr;
+  uint16_t* tl_idx = nullptr;   // one per group entry, then one per group
+  int tl_ust = 0, tl_umax = 0;
+  ld::TileShape tl_shape;
   double lo_hint = 0, hi_hint = 0;
   double lo = 0, hi = 0;    // interval used by the estimators
   size_t bytes = 0;
