@@ -220,6 +220,10 @@ hipError_t launch_spmm(hipStream_t st, const Geom& g, const int* rp, const int* 
                        const double* smult = nullptr, const double* sd = nullptr,
                        const RowGroups* rg = nullptr);
 
+// *out = x^T Q x in FP64 (x[n]; part: kMaxBlocks doubles of scratch).
+hipError_t launch_quad_form(hipStream_t st, int64_t n, int64_t nnz, const int* rp, const int* ci,
+                            const double* va, const double* x, double* part, double* out);
+
 // part[voff+v][col][block] = mult_v[col] * sum_{rows of block} x_v[row][col] w[row][col],
 // v < nv <= kDotsPerLaunch, or nv <= kDotsWide with one chunk per lane (FP32
 // or FP64 vectors)

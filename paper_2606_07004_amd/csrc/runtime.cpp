@@ -2397,38 +2397,40 @@ ld_status ld_tune_set(ld_matrix* a, const ld_params* p, int32_t spmm_lanes, int3
                       spmm_interleave, spmm_row_stride, step_presub, spmm_row_groups);
 }
 
+// The context's workspace of at least `need` bytes (under est_mu).
+static ld_status ensure_workspace(ld_ctx* ctx, size_t need) {
+  const void* ws0 = ctx->workspace.ptr;
+  const size_t wb0 = ctx->workspace.bytes;
+  const hipError_t e = ctx->workspace.ensure(need);
+  // graphs captured on the old workspace point into freed memory
+  if (ctx->workspace.ptr != ws0 || ctx->workspace.bytes != wb0) ctx->graphs.drop_workspace();
+  if (e != hipSuccess)
+    return set_error(e == hipErrorOutOfMemory ? LD_E_NO_MEMORY : LD_E_DEVICE,
+                     std::string("workspace allocation: ") + hipGetErrorString(e));
+  return LD_OK;
+}
+
 ld_status ld_quad_form(ld_matrix* a, const double* x, double* out) {
   if (!a || !x || !out) return set_error(LD_E_INVALID_ARG, "null argument");
   ld_ctx* ctx = a->ctx;
   std::lock_guard<std::mutex> lk(ctx->est_mu);
   LD_HIP_API(hipSetDevice(ctx->device));
-  const int64_t n = a->n;
-  // x as column 0 of an [n][4] FP64 block (the product kernels' minimum
-  // width); W = Q X with the inner product x^T (Q x) fused in the epilogue
-  const int ld = 4;
-  const Geom g = make_geom(n, ld, 8);
-  std::vector<double> hx((size_t)n * ld, 0.0);
-  for (int64_t i = 0; i < n; ++i) hx[(size_t)i * ld] = x[i];
-  DeviceBuffer buf;
-  const size_t vec = (size_t)n * ld * 8;
-  const size_t part = (size_t)kMaxBlocks * ld * 8;
-  LD_HIP_API(buf.ensure(2 * vec + part + 64));
-  char* base = static_cast<char*>(buf.ptr);
+  // x, the blocks' sums and the result in the context's workspace (kept
+  // between calls; the estimates' buffers, which the calls of a context use
+  // one at a time)
+  const size_t vec = align_up((size_t)a->n * 8), part = (size_t)kMaxBlocks * 8;
+  const ld_status rc = ensure_workspace(ctx, vec + part + 64);
+  if (rc != LD_OK) return rc;
+  char* base = static_cast<char*>(ctx->workspace.ptr);
   double* X = reinterpret_cast<double*>(base);
-  double* W = reinterpret_cast<double*>(base + vec);
-  double* pt = reinterpret_cast<double*>(base + 2 * vec);
-  double* res = reinterpret_cast<double*>(base + 2 * vec + part);
-  LD_HIP_API(hipMemcpyAsync(X, hx.data(), vec, hipMemcpyHostToDevice, ctx->stream));
-  VecSet vs{};
-  vs.x[0] = X;
-  int nb = 0;
-  LD_HIP_API(launch_spmm(ctx->stream, g, a->rp, a->ci, a->v64, VT_F64, X, W, nullptr, 1.0, &vs, 1,
-                         0, pt, &nb));
-  LD_HIP_API(launch_reduce(ctx->stream, pt, nb, ld, res));
-  double r[4];
-  LD_HIP_API(hipMemcpyAsync(r, res, sizeof(r), hipMemcpyDeviceToHost, ctx->stream));
+  double* pt = reinterpret_cast<double*>(base + vec);
+  double* res = reinterpret_cast<double*>(base + vec + part);
+  LD_HIP_API(hipMemcpyAsync(X, x, (size_t)a->n * 8, hipMemcpyHostToDevice, ctx->stream));
+  LD_HIP_API(launch_quad_form(ctx->stream, a->n, a->nnz, a->rp, a->ci, a->v64, X, pt, res));
+  double r = 0.0;
+  LD_HIP_API(hipMemcpyAsync(&r, res, sizeof(r), hipMemcpyDeviceToHost, ctx->stream));
   LD_HIP_API(hipStreamSynchronize(ctx->stream));
-  *out = r[0];
+  *out = r;
   return LD_OK;
 }
 
@@ -2455,15 +2457,8 @@ ld_status ld_estimate_detail(ld_matrix* a, const ld_params* p, ld_result* out,
   std::unique_ptr<Run> runp;
   ld_status rc = make_run(runp);
   if (rc != LD_OK) return rc;
-  const size_t need = runp->device_bytes();
-  const void* ws0 = ctx->workspace.ptr;
-  const size_t wb0 = ctx->workspace.bytes;
-  hipError_t e = ctx->workspace.ensure(need);
-  if (e != hipSuccess)
-    return set_error(e == hipErrorOutOfMemory ? LD_E_NO_MEMORY : LD_E_DEVICE,
-                     std::string("workspace allocation: ") + hipGetErrorString(e));
-  // graphs captured on the old workspace point into freed memory
-  if (ctx->workspace.ptr != ws0 || ctx->workspace.bytes != wb0) ctx->graphs.drop_workspace();
+  rc = ensure_workspace(ctx, runp->device_bytes());
+  if (rc != LD_OK) return rc;
   rc = runp->bind(ctx->workspace.ptr, ctx->workspace.bytes);
   if (rc != LD_OK) return rc;
   GraphCache& gc = ctx->graphs;

@@ -76,3 +76,32 @@ def test_quad_form_ragged(L):
         got = L.ld_quad_form(h, x)
         c.release(h)
     assert got == pytest.approx(float(x @ (q @ x)), rel=1e-12)
+
+
+@pytest.mark.parametrize("name", ["one", "diag", "lap2d", "grid", "long_rows", "ragged"])
+def test_quad_form_shapes(L, name):
+    # lanes per row from 2 (short rows) to 64 (rows of 500 entries), rows
+    # without a full group of four entries per lane, one row, more rows than
+    # one pass of the grid
+    rng = np.random.Generator(np.random.PCG64(3))
+    a = {"one": lambda: W.diag_matrix([2.5]),
+         "diag": lambda: W.diag_matrix(rng.uniform(1, 2, 70001)),
+         "lap2d": lambda: W.lap2d(411, 0.1),
+         "grid": lambda: W.wendland_grid(37, 41, 5.0),
+         "long_rows": lambda: W.from_dense(W.random_spd_dense(501, 5)),
+         "ragged": lambda: W.er_laplacian(1003, 9000, seed=4)}[name]()
+    x = rng.standard_normal(a.n)
+    print(f"\n[case] quad form {name} n={a.n} nnz={a.nnz}", flush=True)
+    with L.Context(0) as c:
+        h = c.matrix(a)
+        est = L.ld_estimate_ex(h, L.make_params(8, 2, 1, 1, 7)) if a.n > 1 else None
+        got = L.ld_quad_form(h, x)
+        assert L.ld_quad_form(h, x) == got  # a fixed summation order
+        if est is not None:  # the shared workspace leaves estimates alone
+            assert L.ld_estimate_ex(h, L.make_params(8, 2, 1, 1, 7)).logdet == est.logdet
+    q = a.to_scipy().astype(np.longdouble)
+    xl = x.astype(np.longdouble)
+    want = float(xl @ (q @ xl))
+    # about 100 roundings (2^-53 each) of partial sums bounded by sum |x_i a_ij x_j|
+    bound = float(np.abs(x) @ (abs(a.to_scipy()) @ np.abs(x)))
+    assert abs(got - want) <= 1e-13 * bound
