@@ -114,7 +114,15 @@ __global__ __launch_bounds__(kThreads) void k_gaussian(uint64_t seed, const uint
 // the update's arithmetic, so the update does not read it again; the inner
 // products above then see the reduced W, as modified Gram-Schmidt would.
 // ---------------------------------------------------------------------------
-template <typename VT, typename XT, int C, int NF, bool SPLIT>
+// LAT: the instance for few chunks of rows per block (a small matrix, where
+// the kernel is one chain of memory latencies): four entries' gathers in
+// flight instead of two, the subtracted vector read with the entries, and the
+// block's barrier on the column factors only before the first epilogue (46^3
+// rows, 30 FP32 probes: 16.8 -> 13.4 us; 4096 rows, 30 FP64 probes: 6.4 -> 6.0
+// us).  It takes more registers, and where the gathers of other waves hide the
+// latency it is slower (a random graph of 1e6 rows by 1% of the estimate, 97^3
+// rows with 64 probes by 1.5%).
+template <typename VT, typename XT, int C, int NF, bool SPLIT, bool LAT>
 __device__ inline void spmm_body(int64_t n, int Lr, int lgES_arg, const int* __restrict__ rp,
                                  const int* __restrict__ ci, const VT* __restrict__ va,
                                  const XT* __restrict__ X, XT* __restrict__ W, int ld, int ncolv,
@@ -135,6 +143,7 @@ __device__ inline void spmm_body(int64_t n, int Lr, int lgES_arg, const int* __r
   // registers, with the LDS array used for the final column sums
   constexpr bool LDSACC = NF == 1;
   constexpr int ND = (FUSED && !LDSACC) ? NF : 1;
+  static_assert(!LAT || (C == 1 && !SPLIT), "one chunk per lane, no entry split");
   // sparse entries whose (column, value) a lane loads per round
   constexpr int KE = C >= 3 ? 2 : 4;
   __shared__ double red[FUSED ? kThreads * VEC * C : 1];
@@ -162,7 +171,7 @@ __device__ inline void spmm_body(int64_t n, int Lr, int lgES_arg, const int* __r
         for (int e = 0; e < VEC; ++e) red[red_slot<C, VEC>(rm, c, e)] = 0.0;
     }
   }
-  __syncthreads();
+  if constexpr (!LAT) __syncthreads();
   double dacc[ND][C][VEC];
 #pragma unroll
   for (int v = 0; v < ND; ++v)
@@ -189,9 +198,17 @@ __device__ inline void spmm_body(int64_t n, int Lr, int lgES_arg, const int* __r
       const int t = ch / segs, q = ch - t * segs;
       row = (t * 4 + wv) * ts + q * rpw + rw;
     }
-    if (!rm.on || ch >= nchunk || row >= nn) continue;
+    const bool live = rm.on && ch < nchunk && row < nn;
+    if constexpr (!LAT) {
+      if (!live) continue;
+    }
     A acc[C][VEC];
     V16<XT> xd[FUSED ? C : 1];
+    V16<XT> xs0;
+    if (!LAT || live) {
+    if constexpr (LAT) {
+      if (sx && okc[0]) xs0.load_nt(sx + (size_t)row * ld + colc[0]);
+    }
 #pragma unroll
     for (int c = 0; c < C; ++c)
 #pragma unroll
@@ -218,6 +235,20 @@ __device__ inline void spmm_body(int64_t n, int Lr, int lgES_arg, const int* __r
             if (c1 == row) xd[c] = x1[c];
           }
         }
+    };
+    // four entries' gathers in flight (LAT)
+    auto step4 = [&](const int (&cc)[4], const A (&aa)[4]) {
+      if (okc[0]) {
+        V16<XT> x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u].load(X + (size_t)cc[u] * ld + colc[0]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) acc[0][e] = fma(aa[u], A(x[u].v[e]), acc[0][e]);
+          if (FUSED && cc[u] == row) xd[0] = x[u];
+        }
+      }
     };
     auto step1 = [&](int c0, A a0) {
 #pragma unroll
@@ -254,6 +285,18 @@ __device__ inline void spmm_body(int64_t n, int Lr, int lgES_arg, const int* __r
         if (cnt <= 0) break;
         if (ES == 1) {
           int j = 0;
+          if constexpr (LAT) {
+            for (; j + 4 <= cnt; j += 4) {
+              int cc[4];
+              A aa[4];
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                cc[i] = __shfl(myc[u], rm.lb + j + i);
+                aa[i] = __shfl(mya[u], rm.lb + j + i);
+              }
+              step4(cc, aa);
+            }
+          }
           for (; j + 2 <= cnt; j += 2)
             step2(__shfl(myc[u], rm.lb + j), __shfl(mya[u], rm.lb + j),
                   __shfl(myc[u], rm.lb + j + 1), __shfl(mya[u], rm.lb + j + 1));
@@ -293,6 +336,11 @@ __device__ inline void spmm_body(int64_t n, int Lr, int lgES_arg, const int* __r
           if (okc[c]) xd[c].load(X + (size_t)row * ld + colc[c]);
       }
     }
+    }
+    if constexpr (LAT) {
+      if (j == 0) __syncthreads();
+      if (!live) continue;
+    }
 #pragma unroll
     for (int c = 0; c < C; ++c)
       if (okc[c] && rm.eg == 0) {
@@ -300,7 +348,10 @@ __device__ inline void spmm_body(int64_t n, int Lr, int lgES_arg, const int* __r
         const A* sce = scs + colc[c];
         if (sx) {
           V16<XT> xs;
-          xs.load_nt(sx + (size_t)row * ld + colc[c]);  // read once per step
+          if constexpr (LAT)
+            xs = xs0;
+          else
+            xs.load_nt(sx + (size_t)row * ld + colc[c]);  // read once per step
           const U* cfe = scf + colc[c];
 #pragma unroll
           for (int e = 0; e < VEC; ++e)
@@ -346,7 +397,7 @@ __device__ inline void spmm_body(int64_t n, int Lr, int lgES_arg, const int* __r
 // the grid belong to request r (a single product is a batch of one).  Three
 // or more chunks per lane take 5 blocks per CU instead of 6 (their gathers
 // then fit the registers without spills to scratch).
-template <typename VT, typename XT, int C, int NF, bool SPLIT>
+template <typename VT, typename XT, int C, int NF, bool SPLIT, bool LAT>
 __global__ __launch_bounds__(kThreads, (NF == 2 || (sizeof(VT) == 8 && sizeof(XT) < 8))
                                            ? 4
                                            : (C >= 3 ? 5 : 6)) void k_spmm(
@@ -354,7 +405,7 @@ __global__ __launch_bounds__(kThreads, (NF == 2 || (sizeof(VT) == 8 && sizeof(XT
   int r = 0;
   while (r + 1 < bt.count && (int)blockIdx.x >= bt.off[r + 1]) ++r;
   const SpmmDesc& q = bt.d[r];
-  spmm_body<VT, XT, C, NF, SPLIT>(q.n, q.L, q.lgES, q.rp, q.ci, static_cast<const VT*>(q.va),
+  spmm_body<VT, XT, C, NF, SPLIT, LAT>(q.n, q.L, q.lgES, q.rp, q.ci, static_cast<const VT*>(q.va),
                            static_cast<const XT*>(q.X), static_cast<XT*>(q.W), q.ld, q.ncolv, q.xmult,
                            q.opscale, q.fx, q.fmult, q.voff, q.part, (int)blockIdx.x - bt.off[r],
                            bt.off[r + 1] - bt.off[r], q.il, q.ts, static_cast<const XT*>(q.sx), q.smult,
@@ -498,7 +549,7 @@ __global__ __launch_bounds__(kThreads) void k_dots(int64_t n, int Lr, const XT* 
 // dhole > 0 the vectors skip coefficient row voff + dhole - 1 (a vector the
 // product already subtracted).
 // ---------------------------------------------------------------------------
-template <typename XT, int C, int NV, bool V1, bool SYM>
+template <typename XT, int C, int NV, bool V1, bool SYM, bool PRE>
 __device__ inline void update_body(int64_t n, int Lr, XT* __restrict__ W, int ld, int ncolv,
                                    const void* const* vx, const double* const* vmult, int nv,
                                    const double* __restrict__ d, int voff, int dhole,
@@ -512,12 +563,6 @@ __device__ inline void update_body(int64_t n, int Lr, XT* __restrict__ W, int ld
   __shared__ double red[kThreads * VEC * C];
   __shared__ U cf[NV * kMaxLd];
   const RowMap rm = RowMap::lanes(Lr, 0);
-  for (int i = threadIdx.x; i < NV * ld; i += kThreads) {
-    const int v = i / ld, col = i - v * ld;
-    const int dr = voff + v + ((dhole > 0 && v >= dhole - 1) ? 1 : 0);
-    cf[i] = U(v < nv ? d[(size_t)dr * ld + col] * (vmult[v] ? vmult[v][col] : 1.0) : 0.0);
-  }
-  __syncthreads();
   bool okc[C];
   int colc[C];
 #pragma unroll
@@ -541,18 +586,44 @@ __device__ inline void update_body(int64_t n, int Lr, XT* __restrict__ W, int ld
     }
   const int nn = (int)n;  // n < 2^31
   const int nchunk = (nn + rm.rpi - 1) / rm.rpi;
+  auto coefficients = [&]() {
+    for (int i = threadIdx.x; i < NV * ld; i += kThreads) {
+      const int v = i / ld, col = i - v * ld;
+      const int dr = voff + v + ((dhole > 0 && v >= dhole - 1) ? 1 : 0);
+      cf[i] = U(v < nv ? d[(size_t)dr * ld + col] * (vmult[v] ? vmult[v][col] : 1.0) : 0.0);
+    }
+    __syncthreads();
+  };
+  static_assert(!PRE || (NV == 1 && !V1), "one vector, no v1");
+  if constexpr (!PRE) coefficients();
   for (int j = 0; j * nbk < nchunk; ++j) {
     // a pure stream: consecutive chunks go to consecutive blocks (so the
     // XCDs interleave), which streams faster than the XCD bands the product
     // uses for its neighbour gathers
     const int ch = j * nbk + bk;
     const int row = ch * rm.rpi + rm.rg;
-    if (!rm.on || ch >= nchunk || row >= nn) continue;
+    const bool live = rm.on && ch < nchunk && row < nn;
+    V16<XT> wp[PRE ? C : 1], xp[PRE ? C : 1];
+    if constexpr (PRE) {
+      if (live) {
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+          if (okc[c]) {
+            wp[c].load_nt(W + (size_t)row * ld + colc[c]);
+            if (nv > 0) xp[c].load_nt(static_cast<const XT*>(vx[0]) + (size_t)row * ld + colc[c]);
+          }
+      }
+      if (j == 0) coefficients();
+    }
+    if (!live) continue;
 #pragma unroll
     for (int c = 0; c < C; ++c)
       if (okc[c]) {
         V16<XT> w;
-        w.load_nt(W + (size_t)row * ld + colc[c]);  // the product is read once
+        if constexpr (PRE)
+          w = wp[c];
+        else
+          w.load_nt(W + (size_t)row * ld + colc[c]);  // the product is read once
         U wd[VEC];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) wd[e] = U(w.v[e]);
@@ -564,7 +635,10 @@ __device__ inline void update_body(int64_t n, int Lr, XT* __restrict__ W, int ld
             V16<XT> x;
             // every block is read once per launch and a block is far larger
             // than the caches: streaming loads throughout
-            x.load_nt(static_cast<const XT*>(vx[v]) + (size_t)row * ld + colc[c]);
+            if constexpr (PRE)
+              x = xp[c];
+            else
+              x.load_nt(static_cast<const XT*>(vx[v]) + (size_t)row * ld + colc[c]);
             const U* cfv = cf + v * ld + colc[c];
 #pragma unroll
             for (int e = 0; e < VEC; ++e) wd[e] = fma(-cfv[e], U(x.v[e]), wd[e]);
@@ -622,13 +696,15 @@ template <typename XT, int C, int V1E = C * V16<XT>::N>
 constexpr int update_min_blocks(bool v1) {
   return !v1 ? 4 : (V1E > 24 ? 1 : (V1E > 12 ? 2 : (V1E > 8 ? 3 : 4)));
 }
-template <typename XT, int C, int NV, bool V1, bool SYM>
+// PRE (one vector: window 2): a row's loads come before the first round's
+// coefficients, whose latency they then share.
+template <typename XT, int C, int NV, bool V1, bool SYM, bool PRE>
 __global__ __launch_bounds__(kThreads, (update_min_blocks<XT, C>(V1))) void k_update(
     BatchArgs<UpdDesc> bt) {
   int r = 0;
   while (r + 1 < bt.count && (int)blockIdx.x >= bt.off[r + 1]) ++r;
   const UpdDesc& q = bt.d[r];
-  update_body<XT, C, NV, V1, SYM>(q.n, q.L, static_cast<XT*>(q.W), q.ld, q.ncolv, q.vx, q.vmult,
+  update_body<XT, C, NV, V1, SYM, PRE>(q.n, q.L, static_cast<XT*>(q.W), q.ld, q.ncolv, q.vx, q.vmult,
                                   q.nv, q.d, q.voff, q.dhole, q.want_norm, static_cast<const XT*>(q.v1),
                                   q.v1mult, q.part, (int)blockIdx.x - bt.off[r],
                                   bt.off[r + 1] - bt.off[r]);
@@ -644,19 +720,53 @@ __device__ inline double wave_sum_fixed(double s) {
   return s;
 }
 
+// s[i] += the lane's elements b0 + lane, b0 + lane + 64, ... of p[i][b0 .. nblk)
+// in order, NS streams at once, at most U per lane: their loads are in flight
+// together, also in a partial round (clamped indices; the lane's absent
+// elements add an exact zero).
+template <int NS, int U, bool FULL>
+__device__ inline void lane_sums(const double* const (&p)[NS], int b0, int nblk, int lane,
+                                 double (&s)[NS]) {
+  double v[NS][U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int b = b0 + 64 * u + lane;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) v[i][u] = p[i][FULL ? b : min(b, nblk - 1)];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+      s[i] += (FULL || b0 + 64 * u + lane < nblk) ? v[i][u] : 0.0;
+}
+// All of p[i][0 .. nblk): whole rounds of 8 per lane, then one partial round
+// of no more loads than it needs (a loop over the remainder, one load at a
+// time, cost a memory latency per element: 3.7 -> 3.0 us for the reductions
+// of a small matrix).
+template <int NS>
+__device__ inline void lane_sums_all(const double* const (&p)[NS], int nblk, int lane,
+                                     double (&s)[NS]) {
+  int b0 = 0;
+  for (; b0 + 512 <= nblk; b0 += 512) lane_sums<NS, 8, true>(p, b0, nblk, lane, s);
+  const int left = nblk - b0;
+  if (left > 256) lane_sums<NS, 8, false>(p, b0, nblk, lane, s);
+  else if (left > 64) lane_sums<NS, 4, false>(p, b0, nblk, lane, s);
+  else if (left > 0) lane_sums<NS, 1, false>(p, b0, nblk, lane, s);
+}
+
 __device__ inline double row_sum(const double* __restrict__ p, int nblk, int lane) {
-  double s = 0.0;
-  // unrolled so that the loads are in flight together; the sum keeps its order
-#pragma unroll 8
-  for (int b = lane; b < nblk; b += 64) s += p[b];
-  return wave_sum_fixed(s);
+  const double* const q[1] = {p};
+  double s[1] = {0.0};
+  lane_sums_all<1>(q, nblk, lane, s);
+  return wave_sum_fixed(s[0]);
 }
 
 // One wave per output; outputs off[r] .. off[r+1]-1 belong to batch entry r.
 __global__ __launch_bounds__(kThreads) void k_reduce(BatchArgs<RedDesc> bt) {
   const int lane = threadIdx.x & 63;
   const int o = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  if (o >= bt.off[bt.count]) return;
+  if (o >= bt.off[kMaxBatch]) return;
   int r = 0;
   while (r + 1 < bt.count && o >= bt.off[r + 1]) ++r;
   const RedDesc& q = bt.d[r];
@@ -700,7 +810,7 @@ __global__ __launch_bounds__(kThreads) void k_start_finish(int B, int ld, const 
 __global__ __launch_bounds__(kThreads) void k_step_finish(BatchArgs<FinDesc> bt) {
   const int lane = threadIdx.x & 63;
   const int o = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  if (o >= bt.off[bt.count]) return;
+  if (o >= bt.off[kMaxBatch]) return;
   int r = 0;
   while (r + 1 < bt.count && o >= bt.off[r + 1]) ++r;
   const FinDesc& q = bt.d[r];
@@ -716,30 +826,58 @@ __global__ __launch_bounds__(kThreads) void k_step_finish(BatchArgs<FinDesc> bt)
   double* __restrict__ mult_next = q.mult_next;
   double* __restrict__ g = q.g;
   int* __restrict__ flags = q.flags;
-  const double nrm2 = row_sum(part + (size_t)p * nblk, nblk, lane);
-  const double gdot = g ? row_sum(part + (size_t)(ld + p) * nblk, nblk, lane) : 0.0;
-  const double gin = (g && q.gin_mult) ? row_sum(part + (size_t)(3 * ld + p) * nblk, nblk, lane) : 0.0;
-  const double sdot = sym_row >= 0 ? row_sum(part + (size_t)(2 * ld + p) * nblk, nblk, lane) : 0.0;
-  if (lane != 0) return;
-  // the window inner products of this step are read below before d[sym_row]
-  // (a row of the same array, for the next step) is written
-  double* dsym = sym_row >= 0 ? d + (size_t)sym_row * ld + p : nullptr;
-  if (p >= B || !active[p]) {
-    mult_next[p] = 0.0;
-    if (dsym) *dsym = 0.0;
+  // every load of the step before the first sum: the kernel is one chain of
+  // memory latencies (a wave per probe column, the partials just written by
+  // another kernel), and reading sums, flags and window products one after
+  // the other made it 6.3-7.9 us per step
+  const bool sym = sym_row >= 0, gin = g && q.gin_mult;
+  const int act = p < B ? active[p] : 0;
+  const double ginm = gin ? q.gin_mult[p] : 0.0;
+  // lane v: window product v (and v + 64, ... below)
+  double h0 = lane < nv ? d[(size_t)lane * ld + p] : 0.0;
+  const double* p0 = part + (size_t)p * nblk;
+  const double* p2 = sym ? part + (size_t)(2 * ld + p) * nblk : p0;
+  double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+  if (g) {
+    const double* const ps[4] = {p0, part + (size_t)(ld + p) * nblk, p2,
+                                 gin ? part + (size_t)(3 * ld + p) * nblk : p0};
+    double ss[4] = {0.0, 0.0, 0.0, 0.0};
+    lane_sums_all<4>(ps, nblk, lane, ss);
+    s0 = ss[0];
+    s1 = wave_sum_fixed(ss[1]);
+    s2 = ss[2];
+    s3 = wave_sum_fixed(ss[3]);
+  } else {
+    const double* const ps[2] = {p0, p2};
+    double ss[2] = {0.0, 0.0};
+    lane_sums_all<2>(ps, nblk, lane, ss);
+    s0 = ss[0];
+    s2 = ss[1];
+  }
+  const double nrm2 = wave_sum_fixed(s0), sdot = wave_sum_fixed(s2), gdot = s1;
+  // the window inner products of this step are read before d[sym_row] (a row
+  // of the same array, for the next step) is written
+  double* dsym = sym ? d + (size_t)sym_row * ld + p : nullptr;
+  if (!act) {
+    if (lane == 0) {
+      mult_next[p] = 0.0;
+      if (dsym) *dsym = 0.0;
+    }
     return;
   }
   // v1^T v_t of this step's input vector (needed even if the step breaks down)
-  if (g && q.gin_mult) g[(size_t)p * (m + 1) + t] = gin * q.gin_mult[p];
+  if (gin && lane == 0) g[(size_t)p * (m + 1) + t] = s3 * ginm;
   double* Hp = H + (size_t)p * (m + 1) * m;
   bool finite = true;
   // the product output, and with it every window inner product and the new
   // vector, is stored at the scale 1 / inv_s (a power of two)
-  for (int v = 0; v < nv; ++v) {
-    const double h = d[(size_t)v * ld + p] * q.inv_s;
+  for (int v = lane; v < nv; v += 64) {
+    const double h = (v < 64 ? h0 : d[(size_t)v * ld + p]) * q.inv_s;
     finite = finite && isfinite(h);
     Hp[(size_t)(j0 + v) * m + t] = h;
   }
+  finite = __all(finite);
+  if (lane != 0) return;
   const double nrm = sqrt(nrm2);  // norm of the stored new vector
   const double beta = nrm * q.inv_s;
   Hp[(size_t)(t + 1) * m + t] = beta;
@@ -1010,14 +1148,24 @@ static int resident_blocks(const void* fn) {
 
 // Grid of a chunk-sweeping kernel: at most one resident wave of blocks, a
 // multiple of 8 from 8 blocks up (see chunk_of).
-int stream_grid(const Geom& g, const void* fn) {
+int stream_grid(const Geom& g, const void* fn, bool even) {
   const int rpi = rows_per_block(g.L);
   // a row-group product sweeps groups of kRowGroup rows the way the others
   // sweep rows
   const int64_t units = g.rg ? (g.n + kRowGroup - 1) / kRowGroup : g.n;
   const int64_t nchunk = (units + rpi - 1) / rpi;
-  int64_t nb = std::min<int64_t>(nchunk, resident_blocks(fn));
-  if (nb >= 8) nb &= ~int64_t(7);
+  const int64_t res = std::min<int64_t>(nchunk, resident_blocks(fn));
+  int64_t nb = res;
+  // even (the streams, and the product of a small matrix), two rounds: no more
+  // blocks than they need (3042 chunks on 2048 resident blocks: 1528 blocks
+  // take two rounds as well), so that the second round is as full as the first
+  // and there are fewer partial sums to reduce (an update at 1.02 rounds 50 ->
+  // 44 us).  With more rounds the resident blocks in flight are worth more
+  // than an even last round (4.1 rounds as 5 even ones: 1.3% of the estimate),
+  // and so they are for the larger products, bound by gathers (at 1.02 rounds
+  // 76 -> 84 us).
+  if (even && nchunk > res && nchunk <= 2 * res) nb = ((nchunk + 1) / 2 + 7) & ~int64_t(7);
+  if (nb >= 8) nb = std::min(nb, std::max<int64_t>(8, res & ~int64_t(7))) & ~int64_t(7);
   return (int)std::max<int64_t>(1, nb);
 }
 
@@ -1252,15 +1400,23 @@ static bool spmm_item_ok(const SpmmItem& it) {
   return true;
 }
 
-template <typename VT, typename XT, int C, int NF, bool SPLIT>
+// One chunk per lane and at most two chunks of rows per resident block: the
+// latency instance (its 6 blocks per CU; the rule depends on the item alone, so
+// a request takes the same instance in every batch).
+static bool spmm_few(const SpmmItem& it) {
+  return it.g.C == 1 && it.g.lges == 0 && !it.g.rg &&
+         (it.g.n + rows_per_block(it.g.L) - 1) / rows_per_block(it.g.L) <= 2 * 6 * 256;
+}
+
+template <typename VT, typename XT, int C, int NF, bool SPLIT, bool LAT = false>
 static hipError_t spmm_launch(hipStream_t st, SpmmItem* items, const int* idx, int cnt) {
-  auto fn = k_spmm<VT, XT, C, NF, SPLIT>;
+  auto fn = k_spmm<VT, XT, C, NF, SPLIT, LAT>;
   BatchArgs<SpmmDesc> bt{};
   bt.count = cnt;
   int off = 0;
   for (int q = 0; q < cnt; ++q) {
     SpmmItem& it = items[idx[q]];
-    const int nb = stream_grid(it.g, (const void*)fn);
+    const int nb = stream_grid(it.g, (const void*)fn, LAT);
     it.nblk = nb;
     SpmmDesc& d = bt.d[q];
     d.n = it.g.n;
@@ -1303,6 +1459,8 @@ static hipError_t spmm_launch_c(hipStream_t st, int C, SpmmItem* items, const in
     if (C == 2) return spmm_launch<VT, XT, 2, NF, true>(st, items, idx, cnt);
     return hipErrorInvalidValue;
   }
+  if (spmm_few(items[idx[0]]))
+    return spmm_launch<VT, XT, 1, NF, false, true>(st, items, idx, cnt);
   LD_DISPATCH_C(C, { e = spmm_launch<VT, XT, CC, NF, false>(st, items, idx, cnt); });
   return e;
 }
@@ -1323,7 +1481,7 @@ hipError_t launch_spmm_batch(hipStream_t st, SpmmItem* items, int count) {
     const int tk = spmm_tile_key(it);  // a tile item's lanes and chunks are its own
     return (uint64_t)it.g.xbytes | ((uint64_t)it.vt << 8) | ((uint64_t)(tk ? 0 : it.g.C) << 16) |
            ((uint64_t)it.nf << 24) | ((uint64_t)(it.g.lges > 0) << 32) |
-           ((uint64_t)it.g.rg << 33) | ((uint64_t)tk << 40);
+           ((uint64_t)it.g.rg << 33) | ((uint64_t)spmm_few(it) << 34) | ((uint64_t)tk << 40);
   };
   return launch_grouped(items, count, key, [&](const int* idx, int cnt) -> hipError_t {
     const SpmmItem& it = items[idx[0]];
@@ -1391,13 +1549,13 @@ hipError_t launch_dots(hipStream_t st, const Geom& g, const void* W, const VecSe
     // the wide launch: one chunk per lane (FP32 or FP64 vectors)
     if (g.xbytes == 4 && g.C == 1) {
       auto fn = k_dots<float, 1, kDotsWide>;
-      const int nb = stream_grid(g, (const void*)fn);
+      const int nb = stream_grid(g, (const void*)fn, true);
       *nblk_out = nb;
       hipLaunchKernelGGL(fn, dim3(nb), dim3(kThreads), 0, st, g.n, g.L,
                          static_cast<const float*>(W), g.ld, g.ncolv, vs, nv, voff, part);
     } else if (g.xbytes == 8 && g.C == 1) {
       auto fn = k_dots<double, 1, kDotsWide>;
-      const int nb = stream_grid(g, (const void*)fn);
+      const int nb = stream_grid(g, (const void*)fn, true);
       *nblk_out = nb;
       hipLaunchKernelGGL(fn, dim3(nb), dim3(kThreads), 0, st, g.n, g.L,
                          static_cast<const double*>(W), g.ld, g.ncolv, vs, nv, voff, part);
@@ -1409,7 +1567,7 @@ hipError_t launch_dots(hipStream_t st, const Geom& g, const void* W, const VecSe
   if (g.xbytes == 8) {
     LD_DISPATCH_C(g.C, {
       auto fn = k_dots<double, CC, kDotsPerLaunch>;
-      const int nb = stream_grid(g, (const void*)fn);
+      const int nb = stream_grid(g, (const void*)fn, true);
       *nblk_out = nb;
       hipLaunchKernelGGL(fn, dim3(nb), dim3(kThreads), 0, st, g.n, g.L,
                          static_cast<const double*>(W), g.ld, g.ncolv, vs, nv, voff, part);
@@ -1417,7 +1575,7 @@ hipError_t launch_dots(hipStream_t st, const Geom& g, const void* W, const VecSe
   } else if (g.xbytes == 4) {
     LD_DISPATCH_C(g.C, {
       auto fn = k_dots<float, CC, kDotsPerLaunch>;
-      const int nb = stream_grid(g, (const void*)fn);
+      const int nb = stream_grid(g, (const void*)fn, true);
       *nblk_out = nb;
       hipLaunchKernelGGL(fn, dim3(nb), dim3(kThreads), 0, st, g.n, g.L,
                          static_cast<const float*>(W), g.ld, g.ncolv, vs, nv, voff, part);
@@ -1425,7 +1583,7 @@ hipError_t launch_dots(hipStream_t st, const Geom& g, const void* W, const VecSe
   } else {
     LD_DISPATCH_C(g.C, {
       auto fn = k_dots<_Float16, CC, kDotsPerLaunch>;
-      const int nb = stream_grid(g, (const void*)fn);
+      const int nb = stream_grid(g, (const void*)fn, true);
       *nblk_out = nb;
       hipLaunchKernelGGL(fn, dim3(nb), dim3(kThreads), 0, st, g.n, g.L,
                          static_cast<const _Float16*>(W), g.ld, g.ncolv, vs, nv, voff, part);
@@ -1450,15 +1608,26 @@ static bool update_item_ok(const UpdateItem& it) {
 // 8 (FP32 and FP64 vectors; FP16 vectors take windows up to 4)
 static int update_nv_class(int nv) { return nv <= 1 ? 1 : (nv == 2 ? 2 : (nv <= 4 ? 4 : 8)); }
 
-template <typename XT, int C, int NV, bool V1, bool SYM>
+// PRE where it was faster: FP64 vectors of at most 4 chunks per lane (80^3
+// rows, 96 probes: 195 -> 187 us), and few chunks of rows per block with at most 8
+// elements per lane (a small matrix: 4096 rows, 30 FP64 probes, 5.1 -> 4.9 us).
+// With FP32 vectors on large matrices it cost 107 -> 109 us (97^3 rows, 64
+// probes) and, with 12 elements, 49 -> 51 us (61^3 rows, 96 probes).
+static bool update_pre(const UpdateItem& it) {
+  if (it.nv > 1 || it.v1) return false;
+  const int64_t nchunk = (it.g.n + rows_per_block(it.g.L) - 1) / rows_per_block(it.g.L);
+  return it.g.xbytes == 8 || (it.g.C * it.g.vec <= 8 && nchunk <= 2 * kMaxBlocks);
+}
+
+template <typename XT, int C, int NV, bool V1, bool SYM, bool PRE = false>
 static hipError_t update_launch(hipStream_t st, UpdateItem* items, const int* idx, int cnt) {
-  auto fn = k_update<XT, C, NV, V1, SYM>;
+  auto fn = k_update<XT, C, NV, V1, SYM, PRE>;
   BatchArgs<UpdDesc> bt{};
   bt.count = cnt;
   int off = 0;
   for (int q = 0; q < cnt; ++q) {
     UpdateItem& it = items[idx[q]];
-    const int nb = stream_grid(it.g, (const void*)fn);
+    const int nb = stream_grid(it.g, (const void*)fn, true);
     it.nblk = nb;
     UpdDesc& d = bt.d[q];
     d.n = it.g.n;
@@ -1490,6 +1659,12 @@ template <typename XT, int NV, bool V1, bool SYM>
 static hipError_t update_launch_c(hipStream_t st, int C, UpdateItem* items, const int* idx,
                                   int cnt) {
   hipError_t e = hipErrorInvalidValue;
+  if constexpr (NV == 1 && !V1) {
+    if (update_pre(items[idx[0]])) {
+      LD_DISPATCH_C(C, { e = update_launch<XT, CC, NV, V1, SYM, true>(st, items, idx, cnt); });
+      return e;
+    }
+  }
   LD_DISPATCH_C(C, { e = update_launch<XT, CC, NV, V1, SYM>(st, items, idx, cnt); });
   return e;
 }
@@ -1525,7 +1700,7 @@ hipError_t launch_update_batch(hipStream_t st, UpdateItem* items, int count) {
   auto key = [](const UpdateItem& it) -> uint64_t {
     return (uint64_t)it.g.xbytes | ((uint64_t)it.g.C << 8) |
            ((uint64_t)update_nv_class(it.nv) << 16) | ((uint64_t)(it.v1 != nullptr) << 24) |
-           ((uint64_t)it.sym << 25);
+           ((uint64_t)it.sym << 25) | ((uint64_t)update_pre(it) << 26);
   };
   return launch_grouped(items, count, key, [&](const int* idx, int cnt) -> hipError_t {
     const UpdateItem& it = items[idx[0]];
@@ -1573,7 +1748,7 @@ hipError_t launch_reduce_batch(hipStream_t st, const ReduceItem* items, int coun
       bt.off[q] = off;
       off += it.width;
     }
-    bt.off[cnt] = off;
+    for (int q = cnt; q <= kMaxBatch; ++q) bt.off[q] = off;
     hipLaunchKernelGGL(k_reduce, dim3((off + 3) / 4), dim3(kThreads), 0, st, bt);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -1636,7 +1811,7 @@ hipError_t launch_step_finish_batch(hipStream_t st, const FinishItem* items, int
       bt.off[q] = off;
       off += it.ld;
     }
-    bt.off[cnt] = off;
+    for (int q = cnt; q <= kMaxBatch; ++q) bt.off[q] = off;
     hipLaunchKernelGGL(k_step_finish, dim3((off + 3) / 4), dim3(kThreads), 0, st, bt);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

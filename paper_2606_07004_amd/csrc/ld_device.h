@@ -196,6 +196,9 @@ __device__ inline void red_partials(const double* red, const RowMap& rm, int ld,
   const int WC = rm.Lc * C * VEC;
   for (int i = threadIdx.x; i < WC; i += kThreads) {
     double sum = 0.0;
+    // unrolled so that the LDS reads are in flight together; the sum keeps its
+    // order
+#pragma unroll 8
     for (int q = 0; q < rm.rpi; ++q) sum += red[q * WC + i];
     if (i < ld) part[(row0 + i) * nbk + bk] = sum * (mult ? mult[i] : 1.0);
   }

@@ -318,8 +318,9 @@ hipError_t launch_spmm_rg_group(hipStream_t st, SpmmItem* items, const int* idx,
 int spmm_tile_key(const SpmmItem& it);
 hipError_t launch_spmm_tile_group(hipStream_t st, SpmmItem* items, const int* idx, int cnt);
 // Grid of a streaming kernel `fn` over g's rows (row groups with g.rg): at
-// most one resident wave of blocks, a multiple of 8 from 8 blocks up.
-int stream_grid(const Geom& g, const void* fn);
+// most one resident wave of blocks, a multiple of 8 from 8 blocks up; even: two
+// rounds of chunks on as many blocks as they need.
+int stream_grid(const Geom& g, const void* fn, bool even = false);
 hipError_t launch_update_batch(hipStream_t st, UpdateItem* items, int count);
 hipError_t launch_reduce_batch(hipStream_t st, const ReduceItem* items, int count);
 hipError_t launch_step_finish_batch(hipStream_t st, const FinishItem* items, int count);
