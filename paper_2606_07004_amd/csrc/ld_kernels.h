@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include "ld_device.h"
+#include "band_walk.h"
 #include "row_tiles.h"
 
 namespace ld {
@@ -46,6 +47,8 @@ struct Geom {
                    // per wave (64 / L): the block's 4 waves take rows S apart (one
                    // tile of 4 rows of S rows), so a stencil's +-S neighbours of
                    // one wave's rows are the rows its sibling waves gather
+  int band = 0;    // product only: 0, or a frequent stride P of the matrix (BandMap); used
+                   // with xil = ts = lges = rg = 0
   int rg = 0;      // product only: 1 = the matrix's row groups (RowGroups below)
                    // instead of its CSR rows; FP32 values on FP32 vectors or
                    // FP64 values on FP64 or FP32 vectors, C <= 2, no entry
@@ -112,6 +115,8 @@ struct BatchArgs {
   D d[kMaxBatch];
 };
 
+constexpr int kBandStride = 2048;  // strides from here on make bands (spmm_bands)
+
 struct SpmmDesc {
   int64_t n;
   const int* rp;
@@ -127,6 +132,7 @@ struct SpmmDesc {
   int L, lgES, ld, ncolv, voff;  // L lanes per row (see Geom)
   int il;                        // Geom::xil
   int ts;                        // Geom::ts
+  BandMap bands;                 // Geom::band, where it pays
   // optional early subtraction W -= sd[col] * smult[col] * sx[row][col]
   // (a window vector whose coefficient is known before the product)
   const void* sx;

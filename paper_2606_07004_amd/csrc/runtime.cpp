@@ -469,6 +469,11 @@ bool Run::presub_choice(int ld) const {
   return it == a_->tune.end() || it->second.first == 0;
 }
 
+Geom Run::with_band(Geom g) const {
+  g.band = a_->band;
+  return g;
+}
+
 Geom Run::krylov_geom(int ld, int which) const {
   const int vt = mixed_ ? a_->vt_lo : VT_F64;
   {
@@ -480,7 +485,7 @@ Geom Run::krylov_geom(int ld, int which) const {
       g.xil = (it->second.first >> 12) & 1;    // chunk mapping of the product
       g.ts = (it->second.first >> 16) & 0x7fff;  // row tiles of the product
       g.rg = (it->second.first >> 13) & 1;       // row groups of the product
-      if (geom_usable(g) && (g.rg == 0 || rg_ok())) return g;
+      if (geom_usable(g) && (g.rg == 0 || rg_ok())) return which == 0 ? with_band(g) : g;
     }
   }
   if (which == 0 && rg_ok() && ld >= 16 && !(mixed_ && a_->vt_lo == VT_F64)) {
@@ -517,9 +522,9 @@ Geom Run::krylov_geom(int ld, int which) const {
     // wave busy than the power of two above it (96 probes: 5 rows of 12
     // lanes per wave instead of 4 of 16 with 4 idle)
     Geom g = make_geom_lc(n_, ld, xb_, d.ncolv, 1);
-    if (geom_usable(g)) return g;
+    if (geom_usable(g)) return with_band(g);
   }
-  return d;
+  return which == 0 ? with_band(d) : d;
 }
 
 // One layout for measuring and for carving: with base == nullptr only the
@@ -1543,7 +1548,7 @@ ld_status Run::tune(hipStream_t st, int reps, ld_tune_result* out) {
     }
     for (int round = 0; round < 3; ++round)
       for (int c = 0; c < nc; ++c) {
-        const Geom g = candidate_geom(n_, ld, xb_, cand[c]);
+        const Geom g = with_band(candidate_geom(n_, ld, xb_, cand[c]));
         int nb = 0;
         float ms = 0.f;
         auto product = [&]() {
@@ -1596,11 +1601,11 @@ ld_status Run::tune(hipStream_t st, int reps, ld_tune_result* out) {
         vun.x[v] = v + 1 == nvn ? X : V;
         vun.mult[v] = mult;
       }
-      const Geom gp = candidate_geom(n_, ld, xb_, cand[bp]);
+      const Geom gp = with_band(candidate_geom(n_, ld, xb_, cand[bp]));
       const Geom gu = candidate_geom(n_, ld, xb_, cand[bu]);
       std::vector<int> ucand;
       for (int c = 0; c < nc; ++c) {
-        const Geom g = candidate_geom(n_, ld, xb_, cand[c]);
+        const Geom g = with_band(candidate_geom(n_, ld, xb_, cand[c]));
         if (g.lges == 0 && g.xil == 0 && g.ts == 0 && g.rg == 0) ucand.push_back(c);
       }
       double t_psp = 1e300, t_psu = 1e300, t_pp = 1e300;
@@ -1632,7 +1637,7 @@ ld_status Run::tune(hipStream_t st, int reps, ld_tune_result* out) {
                                &nb, nv);
         }, t_psu));
         for (int c : ucand) {
-          const Geom g = candidate_geom(n_, ld, xb_, cand[c]);
+          const Geom g = with_band(candidate_geom(n_, ld, xb_, cand[c]));
           LD_HIP(timed([&]() {
             return launch_update(st, g, W, vun, nvn, dcoef, 0, 1, nullptr, nullptr, true, part,
                                  &nb);
@@ -1659,7 +1664,7 @@ ld_status Run::tune(hipStream_t st, int reps, ld_tune_result* out) {
       std::vector<double> tv(nc, 1e300);
       for (int round = 0; round < 3; ++round)
         for (int c = 0; c < nc; ++c) {
-          const Geom g = candidate_geom(n_, ld, xb_, cand[c]);
+          const Geom g = with_band(candidate_geom(n_, ld, xb_, cand[c]));
           if (g.lges != 0 || g.xil != 0 || g.ts != 0 || g.rg != 0) continue;
           int nb = 0;
           auto upd = [&]() {
@@ -2107,6 +2112,30 @@ static hipError_t build_tiles(hipStream_t st, ld_matrix* m, const TileShape& s) 
   return e;
 }
 
+// The row stride that a grid's planes (lines, in 2-D) give the matrix: of the
+// positive column offsets that at least a quarter of 512 sampled rows hold,
+// the middle one of those above half the largest (a wider stencil has several
+// about N^2); 0 below kBandStride and for long rows, whose product splits them.
+static int frequent_stride(int64_t n, int64_t nnz, const int32_t* rp, const int32_t* ci) {
+  constexpr int64_t kWin = 256;
+  if (n < 4 * kWin || nnz >= 64 * n) return 0;
+  std::vector<int32_t> offs;
+  for (const int64_t r0 : {n / 4, n / 2})
+    for (int64_t i = r0; i < r0 + kWin; ++i)
+      for (int32_t k = rp[i]; k < rp[i + 1]; ++k)
+        if (ci[k] - i >= kBandStride / 2) offs.push_back((int32_t)(ci[k] - i));
+  std::sort(offs.begin(), offs.end());
+  std::vector<int32_t> freq;
+  for (size_t i = 0, j = 0; i < offs.size(); i = j) {
+    while (j < offs.size() && offs[j] == offs[i]) ++j;
+    if (j - i >= (size_t)(2 * kWin) / 4) freq.push_back(offs[i]);
+  }
+  if (freq.empty()) return 0;
+  const size_t lo = std::upper_bound(freq.begin(), freq.end(), freq.back() / 2) - freq.begin();
+  const int32_t mid = freq[lo + (freq.size() - lo) / 2];
+  return mid >= kBandStride ? mid : 0;
+}
+
 ld_status ld_create_csr(ld_ctx* ctx, int64_t n, int64_t nnz, const int32_t* row_ptr,
                         const int32_t* col_idx, const double* values, int32_t vt,
                         double lambda_lo_hint, double lambda_hi_hint, ld_matrix** out) {
@@ -2251,6 +2280,7 @@ ld_status ld_create_csr(ld_ctx* ctx, int64_t n, int64_t nnz, const int32_t* row_
         });
     }
   }
+  m->band = frequent_stride(n, nnz, row_ptr, col_idx);
   // row groups (FP32 or FP64 storage; BF16 values keep the CSR product)
   if (e == hipSuccess && (m->vt_lo == VT_F32 || m->vt_lo == VT_F64)) {
     const int64_t ng = (n + kRowGroup - 1) / kRowGroup;

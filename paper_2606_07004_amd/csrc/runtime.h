@@ -172,6 +172,7 @@ struct ld_matrix {
   uint16_t* tl_idx = nullptr;   // one per group entry, then one per group
   int tl_ust = 0, tl_umax = 0;
   ld::TileShape tl_shape;
+  int band = 0;  // frequent stride of the CSR rows from kBandStride on, 0 = none (Geom::band)
   double lo_hint = 0, hi_hint = 0;
   double lo = 0, hi = 0;    // interval used by the estimators
   size_t bytes = 0;
@@ -239,6 +240,7 @@ class Run {
   // product (which = 0) or update (which = 1) geometry of a Krylov block of
   // width ld: the matrix's tuned choice when it holds one, else the default
   Geom krylov_geom(int ld, int which) const;
+  Geom with_band(Geom g) const;   // a product geometry with the matrix's frequent stride
   bool rg_ok() const;             // the product may read the matrix's row groups
   RowGroups row_groups() const;
   int upd_steady_nv(bool presub) const;  // update vectors of a steady-state step
