@@ -281,7 +281,8 @@ __device__ inline void tile_body(const TileDesc& q, int bk0, int nb0) {
       if (r0 < nu) load_lds16(xp + (size_t)m.tc[u] * ld, xs_raw + (size_t)r0 * PB);
     }
     if (nu > TB * NW * RPW) {
-      const int tile = q.il ? j * nbk + bk : chunk_of(j, bk, nbk);
+      // (past the last tile the last one again, as in meta)
+      const int tile = min(q.il ? j * nbk + bk : chunk_of(j, bk, nbk), ntile - 1);
       const int* tc = q.tcol + (size_t)tile * q.ust;
       for (int rb = TB * NW * RPW; rb < nu; rb += TB * NW * RPW) {
         int c[TB];

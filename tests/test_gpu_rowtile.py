@@ -51,6 +51,9 @@ MATS = {
     "grid_41x47": lambda: W.wendland_grid(41, 47, 8.0, nugget=NUG),
     # entries past six rounds of 16 per group and unions too large for LDS
     "grid_30x60_wide": lambda: W.wendland_grid(30, 60, 13.0, nugget=NUG),
+    # 12 tiles on 8 blocks: blocks without a tile in the second round, the last
+    # tile's union beyond the columns of one load round (448 of 320)
+    "grid_16x48_idle": lambda: W.wendland_grid(16, 48, 12.0, nugget=NUG),
     "dense_40x50": lambda: W.wendland_grid(40, 50, 24.0, nugget=0.5),
 }
 
