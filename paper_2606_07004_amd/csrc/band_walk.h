@@ -30,7 +30,7 @@ inline BandMap make_band_map(int64_t stride, int rows_per_chunk) {
 // b % 8) takes every (nbk / 8)-th slot of its XCD's bands, c slots per band.
 struct BandWalk {
   uint64_t m;
-  int c, off, band, doff, dband;
+  int c, off = 0, band = 0, doff = 0, dband = 0;
   LD_HOST_DEVICE inline BandWalk(const BandMap& b, int bk, int nbk) : m(b.m), c(b.c) {
     if (c == 0) return;
     const int w = bk >> 3, nw = nbk >> 3;
@@ -41,19 +41,21 @@ struct BandWalk {
     doff = nw - dband * c;
     dband *= 8;
   }
-  // the next slot's chunk, nchunk for a slot without one; false at the end
-  LD_HOST_DEVICE inline bool next(int nchunk, int* ch) {
-    const int lo = (int)((uint64_t)band * m >> kBandShift);
-    if (lo >= nchunk) return false;
-    const int hi = (int)((uint64_t)(band + 1) * m >> kBandShift);
-    *ch = lo + off < hi ? lo + off : nchunk;
-    band += dband;
-    off += doff;
-    if (off >= c) {
-      off -= c;
-      band += 8;
+  // the next chunk, or nchunk at the end (slots past a band's last chunk are
+  // passed over)
+  LD_HOST_DEVICE inline int next(int nchunk) {
+    for (;;) {
+      const int ch = (int)((uint64_t)band * m >> kBandShift) + off;
+      const int hi = (int)((uint64_t)(band + 1) * m >> kBandShift);
+      if (ch - off >= nchunk) return nchunk;
+      band += dband;
+      off += doff;
+      if (off >= c) {
+        off -= c;
+        band += 8;
+      }
+      if (ch < hi && ch < nchunk) return ch;
     }
-    return true;
   }
 };
 

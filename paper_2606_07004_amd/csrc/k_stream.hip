@@ -190,23 +190,19 @@ __device__ inline void spmm_body(int64_t n, int Lr, int lgES_arg, const int* __r
   const int segs = ts > 0 ? ts / rpw : 1;
   const int tchunks = ts > 0 ? (nn / (4 * ts)) * segs : 0;
   const int wv = (int)threadIdx.x >> 6, rw = rm.rg - wv * rpw;
+  // a contiguous run of each round's chunks per XCD keeps a row's neighbours in
+  // one L2; interleaving streams better on wide rows (a tuning choice)
+  int ch = il ? bk : chunk_of(0, bk, nbk);
+  const bool banded = !LAT && bands.c > 0;
   BandWalk walk(bands, bk, nbk);
-  for (int j = 0;; ++j) {
-    int ch;
-    if (!LAT && walk.c > 0) {
-      if (!walk.next(nchunk, &ch)) break;
-    } else {
-      if (j * nbk >= nchunk) break;
-      // per-XCD bands keep a row's neighbours in one L2; interleaving streams
-      // better on wide rows (a tuning choice)
-      ch = il ? j * nbk + bk : chunk_of(j, bk, nbk);
-    }
+  if (banded) ch = walk.next(nchunk);
+  for (bool first = true; ch < nchunk; ch = banded ? walk.next(nchunk) : ch + nbk) {
     int row = ch * rm.rpi + rm.rg;
     if (ch < tchunks) {
       const int t = ch / segs, q = ch - t * segs;
       row = (t * 4 + wv) * ts + q * rpw + rw;
     }
-    const bool live = rm.on && ch < nchunk && row < nn;
+    const bool live = rm.on && row < nn;
     if constexpr (!LAT) {
       if (!live) continue;
     }
@@ -346,7 +342,8 @@ __device__ inline void spmm_body(int64_t n, int Lr, int lgES_arg, const int* __r
     }
     }
     if constexpr (LAT) {
-      if (j == 0) __syncthreads();
+      if (first) __syncthreads();
+      first = false;
       if (!live) continue;
     }
 #pragma unroll
@@ -604,13 +601,12 @@ __device__ inline void update_body(int64_t n, int Lr, XT* __restrict__ W, int ld
   };
   static_assert(!PRE || (NV == 1 && !V1), "one vector, no v1");
   if constexpr (!PRE) coefficients();
-  for (int j = 0; j * nbk < nchunk; ++j) {
+  for (int ch = bk; ch < nchunk; ch += nbk) {
     // a pure stream: consecutive chunks go to consecutive blocks (so the
     // XCDs interleave), which streams faster than the XCD bands the product
     // uses for its neighbour gathers
-    const int ch = j * nbk + bk;
     const int row = ch * rm.rpi + rm.rg;
-    const bool live = rm.on && ch < nchunk && row < nn;
+    const bool live = rm.on && row < nn;
     V16<XT> wp[PRE ? C : 1], xp[PRE ? C : 1];
     if constexpr (PRE) {
       if (live) {
@@ -621,7 +617,7 @@ __device__ inline void update_body(int64_t n, int Lr, XT* __restrict__ W, int ld
             if (nv > 0) xp[c].load_nt(static_cast<const XT*>(vx[0]) + (size_t)row * ld + colc[c]);
           }
       }
-      if (j == 0) coefficients();
+      if (ch == bk) coefficients();
     }
     if (!live) continue;
 #pragma unroll
@@ -1630,14 +1626,15 @@ static bool update_item_ok(const UpdateItem& it) {
 static int update_nv_class(int nv) { return nv <= 1 ? 1 : (nv == 2 ? 2 : (nv <= 4 ? 4 : 8)); }
 
 // PRE where it was faster: FP64 vectors of at most 4 chunks per lane (80^3
-// rows, 96 probes: 195 -> 187 us), and few chunks of rows per block with at most 8
-// elements per lane (a small matrix: 4096 rows, 30 FP64 probes, 5.1 -> 4.9 us).
-// With FP32 vectors on large matrices it cost 107 -> 109 us (97^3 rows, 64
+// rows, 96 probes: 195 -> 187 us), and up to 24 rounds of resident blocks with
+// at most 8 elements per lane (4096 rows, 30 FP64 probes, 5.1 -> 4.9 us;
+// estimates on 360^2 rows with 64 FP32 probes by 2.2%, 600^2 with 30 by 1.5%).
+// With FP32 vectors on larger matrices it cost 107 -> 109 us (97^3 rows, 64
 // probes) and, with 12 elements, 49 -> 51 us (61^3 rows, 96 probes).
 static bool update_pre(const UpdateItem& it) {
   if (it.nv > 1 || it.v1) return false;
   const int64_t nchunk = (it.g.n + rows_per_block(it.g.L) - 1) / rows_per_block(it.g.L);
-  return it.g.xbytes == 8 || (it.g.C * it.g.vec <= 8 && nchunk <= 2 * kMaxBlocks);
+  return it.g.xbytes == 8 || (it.g.C * it.g.vec <= 8 && nchunk <= 24 * kMaxBlocks);
 }
 
 template <typename XT, int C, int NV, bool V1, bool SYM, bool PRE = false>

@@ -14,9 +14,7 @@ int main() {
     std::printf("%d", b.c);
     for (int bk = 0; bk < nbk; ++bk) {
       ld::BandWalk w(b, bk, nbk);
-      int ch;
-      while (w.next(nchunk, &ch))
-        if (ch < nchunk) std::printf(" %d", ch);
+      for (int ch = w.next(nchunk); ch < nchunk; ch = w.next(nchunk)) std::printf(" %d", ch);
       std::printf(" -1");
     }
     std::printf("\n");
