@@ -524,6 +524,41 @@ Geom Run::krylov_geom(int ld, int which) const {
     Geom g = make_geom_lc(n_, ld, xb_, d.ncolv, 1);
     if (geom_usable(g)) return with_band(g);
   }
+  // Blocks of less than 24 chunks that make_geom gives several chunks per lane:
+  // a load of L < 8 lanes takes less than a 128-byte line of a row, and rows
+  // that are no multiple of the L chunks idle lanes and straddle lines.  One
+  // chunk per lane, for the product as many lanes as chunks (more rows per wave
+  // than the power of two; from 22 on no more rows: 16 x 2), for the update the
+  // power of two.  Estimates on 72^3 rows, product / update / both changed: 3
+  // chunks (1 x 3 before) 0.71 / 0.83 / 0.51 of the time, 6 (2 x 3) 0.76 / 0.75
+  // / 0.52, 10 (4 x 3) 0.80 / 0.76 / 0.57, 12 0.87 / 0.88 / 0.75, 20 (8 x 3)
+  // 0.92 / 0.92 / 0.86, 23 0.94 / 0.79; 24 chunks (8 x 3, whole lines) stay.
+  // On few rows the update keeps fewer, larger blocks, whose sums k_reduce has
+  // to add (13.8K rows: one chunk per lane 1.01 to 1.12 of the time from 9
+  // chunks on, but 0.86 to 0.93 up to 6).
+  if (xb_ != 2 && d.C > 1 && d.ncolv < 24) {
+    int L = 1;
+    while (L < d.ncolv) L <<= 1;
+    if (which == 0) {
+      const Geom g = d.ncolv < 22 ? make_geom_lc(n_, ld, xb_, d.ncolv, 1)
+                                  : make_geom_lc(n_, ld, xb_, L / 2, 2);
+      if (geom_usable(g)) return with_band(g);
+    } else if (d.L < 4 || n_ * L > 2048 * kThreads) {
+      const Geom g = make_geom_lc(n_, ld, xb_, L, 1);
+      if (geom_usable(g)) return g;
+    }
+  }
+  // A product of a wave per row (or, with FP64 vectors, of a full half) over
+  // many rows: two chunks per lane, twice the gathers in flight per lane (52 to
+  // 64 chunks: 72^3 rows 0.95 to 0.97 of the time in FP64, 0.98 to 0.99 in
+  // FP32; 32 chunks 0.98 in FP64, but in FP32 1.00 and, on 300^2 rows, the
+  // product 37 -> 40 us; 25 to 31 chunks lose by the idle lanes).  On fewer
+  // rows one chunk per lane is faster (13.8K rows: 1.02; 240^2 with 32: 1.02).
+  if (which == 0 && xb_ != 2 && d.C == 1 && (d.ncolv >= 52 || (d.ncolv == 32 && xb_ == 8)) &&
+      n_ * d.L > 10 * 1024 * kThreads) {
+    const Geom g = make_geom_lc(n_, ld, xb_, d.L / 2, 2);
+    if (geom_usable(g)) return with_band(g);
+  }
   return which == 0 ? with_band(d) : d;
 }
 
