@@ -488,15 +488,16 @@ Geom Run::krylov_geom(int ld, int which) const {
       if (geom_usable(g) && (g.rg == 0 || rg_ok())) return which == 0 ? with_band(g) : g;
     }
   }
-  if (which == 0 && rg_ok() && ld >= 16 && !(mixed_ && a_->vt_lo == VT_F64)) {
+  if (which == 0 && rg_ok() && ld >= 16 && (!(mixed_ && a_->vt_lo == VT_F64) || a_->tl_col)) {
     // row groups (blocks of 16 columns or more: on narrower ones the groups'
     // extra multiply-adds and shuffles weigh more than the gathers they
     // save): one chunk per lane with FP32 vectors, two with FP64 ones (the
     // 64-probe covariance: 16 x 2 0.55 ms, 32 x 1 0.67 ms per product).
-    // FP64 values on FP32 vectors keep the CSR product by default (their
-    // FP64 sums of 4 rows cost occupancy: on that covariance 22.3 against
-    // 21.3 ms per estimate); the autotuner and ld_tune_set can still take
-    // the groups there
+    // FP64 values on FP32 vectors take them only where the matrix keeps row
+    // tiles (estimates, tiles against the CSR product: scattered covariances of
+    // 3K to 200K rows, 16 to 96 probes, 0.63 to 0.99 of the time, grid ones 0.56
+    // to 0.90); the row-group product's FP64 sums of 4 rows cost it occupancy
+    // (22.3 against 21.3 ms), but the autotuner and ld_tune_set can still take it
     const int ncolv = ld / (16 / xb_);
     const int C = (xb_ == 8 && ncolv >= 4) ? 2 : 1;
     Geom g = make_geom_lc(n_, ld, xb_, (ncolv + C - 1) / C, C);
