@@ -98,3 +98,20 @@ def test_few_chunks(L, ctx, prec, chunks):
 ])
 def test_bands(L, ctx, n, strides, npr, prec, lanes, chunks):
     _compare(L, ctx, _banded(n, strides), npr, prec, lanes, chunks, 1)
+
+
+# sketch widths at the padding of the factorisation's rows to 8 columns, up to
+# its LDS bound of 64 and past it: the basis of two Cholesky-QR passes is
+# orthonormal to the rounding of its n-term sums
+@pytest.mark.parametrize("s", [1, 2, 7, 8, 9, 16, 31, 57, 63, 64, 65])
+def test_sketch_basis(L, ctx, s):
+    n = 900
+    a = _banded(n, (1, 30))
+    h = ctx.matrix(a, vt=L.LD_VT_FP64)
+    try:
+        p = L.make_params(s + 4, s, 8, 2, 3, precision=L.LD_PREC_FP64)
+        q = L.ld_estimate_detail(h, p, n=n, basis=True)[1]["sketch_basis"]
+    finally:
+        ctx.release(h)
+    assert q.shape == (n, s)
+    assert np.max(np.abs(q.T @ q - np.eye(s))) <= 64 * n * 2.0 ** -53
