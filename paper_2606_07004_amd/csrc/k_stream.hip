@@ -568,6 +568,16 @@ __device__ inline void update_body(int64_t n, int Lr, XT* __restrict__ W, int ld
   __shared__ double red[kThreads * VEC * C];
   __shared__ U cf[NV * kMaxLd];
   const RowMap rm = RowMap::lanes(Lr, 0);
+  auto coefficients = [&]() {
+    for (int i = threadIdx.x; i < NV * ld; i += kThreads) {
+      const int v = i / ld, col = i - v * ld;
+      const int dr = voff + v + ((dhole > 0 && v >= dhole - 1) ? 1 : 0);
+      cf[i] = U(v < nv ? d[(size_t)dr * ld + col] * (vmult[v] ? vmult[v][col] : 1.0) : 0.0);
+    }
+    __syncthreads();
+  };
+  static_assert(!PRE || (NV <= 4 && !V1), "at most 4 vectors, no v1");
+  if constexpr (!PRE) coefficients();
   bool okc[C];
   int colc[C];
 #pragma unroll
@@ -591,30 +601,23 @@ __device__ inline void update_body(int64_t n, int Lr, XT* __restrict__ W, int ld
     }
   const int nn = (int)n;  // n < 2^31
   const int nchunk = (nn + rm.rpi - 1) / rm.rpi;
-  auto coefficients = [&]() {
-    for (int i = threadIdx.x; i < NV * ld; i += kThreads) {
-      const int v = i / ld, col = i - v * ld;
-      const int dr = voff + v + ((dhole > 0 && v >= dhole - 1) ? 1 : 0);
-      cf[i] = U(v < nv ? d[(size_t)dr * ld + col] * (vmult[v] ? vmult[v][col] : 1.0) : 0.0);
-    }
-    __syncthreads();
-  };
-  static_assert(!PRE || (NV == 1 && !V1), "one vector, no v1");
-  if constexpr (!PRE) coefficients();
   for (int ch = bk; ch < nchunk; ch += nbk) {
     // a pure stream: consecutive chunks go to consecutive blocks (so the
     // XCDs interleave), which streams faster than the XCD bands the product
     // uses for its neighbour gathers
     const int row = ch * rm.rpi + rm.rg;
     const bool live = rm.on && row < nn;
-    V16<XT> wp[PRE ? C : 1], xp[PRE ? C : 1];
+    V16<XT> wp[PRE ? C : 1], xp[PRE ? NV : 1][PRE ? C : 1];
     if constexpr (PRE) {
       if (live) {
 #pragma unroll
         for (int c = 0; c < C; ++c)
           if (okc[c]) {
             wp[c].load_nt(W + (size_t)row * ld + colc[c]);
-            if (nv > 0) xp[c].load_nt(static_cast<const XT*>(vx[0]) + (size_t)row * ld + colc[c]);
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+              if (v < nv)
+                xp[v][c].load_nt(static_cast<const XT*>(vx[v]) + (size_t)row * ld + colc[c]);
           }
       }
       if (ch == bk) coefficients();
@@ -640,7 +643,7 @@ __device__ inline void update_body(int64_t n, int Lr, XT* __restrict__ W, int ld
             // every block is read once per launch and a block is far larger
             // than the caches: streaming loads throughout
             if constexpr (PRE)
-              x = xp[c];
+              x = xp[v][c];
             else
               x.load_nt(static_cast<const XT*>(vx[v]) + (size_t)row * ld + colc[c]);
             const U* cfv = cf + v * ld + colc[c];
@@ -1630,10 +1633,16 @@ static int update_nv_class(int nv) { return nv <= 1 ? 1 : (nv == 2 ? 2 : (nv <= 
 // at most 8 elements per lane (4096 rows, 30 FP64 probes, 5.1 -> 4.9 us;
 // estimates on 360^2 rows with 64 FP32 probes by 2.2%, 600^2 with 30 by 1.5%).
 // With FP32 vectors on larger matrices it cost 107 -> 109 us (97^3 rows, 64
-// probes) and, with 12 elements, 49 -> 51 us (61^3 rows, 96 probes).
+// probes) and, with 12 elements, 49 -> 51 us (61^3 rows, 96 probes).  Two to
+// four vectors with one chunk per lane: windows 3 and 4 on 350^2 and 507^2
+// rows, 30 and 64 FP32 probes, 0.96 to 0.99 of the time per estimate, FP64 0.97
+// to 1.00; FP64 at 20 rounds (800^2 rows, 30 probes) 1.01, hence 12.
 static bool update_pre(const UpdateItem& it) {
-  if (it.nv > 1 || it.v1) return false;
+  if (it.nv > 4 || it.v1) return false;
   const int64_t nchunk = (it.g.n + rows_per_block(it.g.L) - 1) / rows_per_block(it.g.L);
+  if (it.nv > 1)
+    return it.g.C == 1 && it.g.xbytes >= 4 &&
+           nchunk <= (it.g.xbytes == 8 ? 12 : 24) * (int64_t)kMaxBlocks;
   return it.g.xbytes == 8 || (it.g.C * it.g.vec <= 8 && nchunk <= 24 * kMaxBlocks);
 }
 
@@ -1677,7 +1686,7 @@ template <typename XT, int NV, bool V1, bool SYM>
 static hipError_t update_launch_c(hipStream_t st, int C, UpdateItem* items, const int* idx,
                                   int cnt) {
   hipError_t e = hipErrorInvalidValue;
-  if constexpr (NV == 1 && !V1) {
+  if constexpr (NV <= 4 && !V1 && (NV == 1 || sizeof(XT) >= 4)) {
     if (update_pre(items[idx[0]])) {
       LD_DISPATCH_C(C, { e = update_launch<XT, CC, NV, V1, SYM, true>(st, items, idx, cnt); });
       return e;
