@@ -357,7 +357,10 @@ ld_status ld_autotune(ld_matrix* a, const ld_params* p, int32_t reps, ld_tune_re
  * choice found earlier, or one to test): the product with spmm_lanes lanes
  * per row, spmm_chunks chunks per lane, its entries split over
  * spmm_entry_split lane groups and its row chunks interleaved over the XCDs
- * (spmm_interleave 1) or banded per XCD (0), and its rows taken in tiles
+ * (spmm_interleave 1) or banded per XCD (0; on a matrix most of whose rows
+ * hold a column the same 2048 rows or more further on, and without row
+ * tiles, each XCD takes an eighth of every run of that many rows), and its
+ * rows taken in tiles
  * (spmm_row_stride S > 0: each 256-thread block's four waves take runs of
  * 64 / L consecutive rows S rows apart, so on a grid operator whose line
  * stride is S the +-S neighbours of one wave's rows are the rows the other
