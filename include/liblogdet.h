@@ -357,7 +357,7 @@ ld_status ld_autotune(ld_matrix* a, const ld_params* p, int32_t reps, ld_tune_re
  * choice found earlier, or one to test): the product with spmm_lanes lanes
  * per row, spmm_chunks chunks per lane, its entries split over
  * spmm_entry_split lane groups and its row chunks interleaved over the XCDs
- * (spmm_interleave 1) or banded per XCD (0; on a matrix most of whose rows
+ * (spmm_interleave 1) or banded per XCD (0; on a matrix a quarter of whose rows
  * hold a column the same 2048 rows or more further on, and without row
  * tiles, each XCD takes an eighth of every run of that many rows), and its
  * rows taken in tiles
