@@ -6,6 +6,7 @@
 // columns held at zero), so one sparse entry gathers one contiguous run of
 // probe values.  Every reduction goes through per-block partial sums in a
 // fixed order (no floating-point atomics): results are bitwise reproducible.
+#include "entry_walk.h"
 #include "ld_kernels.h"
 #include <type_traits>
 #include "gw_ql.h"
@@ -265,17 +266,19 @@ __device__ inline void spmm_body(int64_t n, int Lr, int lgES_arg, const int* __r
           if (FUSED && c0 == row) xd[c] = x;
         }
     };
-    const int kbeg = rp[row];
-    const int kend = rp[row + 1];
+    // entry positions are unsigned: the round past a row that ends at 2^31 - 1,
+    // the largest entry count of a matrix, starts beyond an int
+    const unsigned kbeg = (unsigned)rp[row];
+    const unsigned kend = (unsigned)rp[row + 1];
     // the row's L lanes load KE * L consecutive entries (column, value) per
     // round, lane l holding entries l, l + L, ..., and pass them around the
     // group by lane shuffles; entries are accumulated in order
-    for (int base = kbeg; base < kend; base += rm.L * KE) {
+    for (unsigned base = kbeg; base < kend; base += (unsigned)(rm.L * KE)) {
       int myc[KE];
       A mya[KE];
 #pragma unroll
       for (int u = 0; u < KE; ++u) {
-        const int kk = base + rm.gl + rm.L * u;
+        const unsigned kk = base + (unsigned)(rm.gl + rm.L * u);
         myc[u] = row;
         mya[u] = A(0);
         if (kk < kend) {
@@ -285,7 +288,7 @@ __device__ inline void spmm_body(int64_t n, int Lr, int lgES_arg, const int* __r
       }
 #pragma unroll
       for (int u = 0; u < KE; ++u) {
-        const int cnt = min(rm.L, kend - base - rm.L * u);
+        const int cnt = min(rm.L, (int)(kend - base) - rm.L * u);
         if (cnt <= 0) break;
         if (ES == 1) {
           int j = 0;
@@ -442,22 +445,22 @@ __global__ __launch_bounds__(kThreads) void k_quad_form(int64_t n, int lgL,
     const int64_t row = (j * gridDim.x + blockIdx.x) * rpb + (threadIdx.x >> lgL);
     double s = 0.0;
     if (row < n) {
-      const int ke = rp[row + 1];
-      int k = rp[row] + l;
-      for (; k + 3 * L < ke; k += 4 * L) {
-        int c[4];
-        double a[4], xv[4];
+      lane_entries(
+          rp[row], rp[row + 1], l, L,
+          [&](unsigned k) {
+            int c[4];
+            double a[4], xv[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          c[u] = __builtin_nontemporal_load(ci + k + u * L);
-          a[u] = __builtin_nontemporal_load(va + k + u * L);
-        }
+            for (int u = 0; u < 4; ++u) {
+              c[u] = __builtin_nontemporal_load(ci + k + u * L);
+              a[u] = __builtin_nontemporal_load(va + k + u * L);
+            }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) xv[u] = x[c[u]];
+            for (int u = 0; u < 4; ++u) xv[u] = x[c[u]];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) s = fma(a[u], xv[u], s);
-      }
-      for (; k < ke; k += L) s = fma(va[k], x[ci[k]], s);
+            for (int u = 0; u < 4; ++u) s = fma(a[u], xv[u], s);
+          },
+          [&](unsigned k) { s = fma(va[k], x[ci[k]], s); });
     }
     for (int d = L >> 1; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
     if (row < n && l == 0) acc = fma(x[row], s, acc);
@@ -1255,8 +1258,8 @@ __global__ __launch_bounds__(kThreads) void k_spmm_signs(int64_t n, int lgL,
     for (int d = L; d < 64; d <<= 1) cnt = max(cnt, __shfl_xor(cnt, d, 64));
     double acc0 = 0.0, acc1 = 0.0;
     for (int base = 0; base < cnt; base += L) {
-      const int k = kb + base + l;
-      const bool have = k < ke;
+      const unsigned k = (unsigned)kb + (unsigned)(base + l);  // may pass 2^31 - 1
+      const bool have = k < (unsigned)ke;
       const int col = have ? ci[k] : 0;
       const double a = have ? value_as<VT, double>(va[k]) : 0.0;
       uint64_t w0 = 0, w1 = 0;
