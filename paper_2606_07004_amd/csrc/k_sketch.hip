@@ -161,7 +161,8 @@ __global__ __launch_bounds__(kThreads) void k_chol_inv(int s, const double* __re
 // roots, divisions and LDS reads), so no step waits on a barrier: lane j owns
 // column j, row k of R is formed from the rows above it (the same subtractions
 // in the same order as in chol_inv_body), the pivot's root is taken by every
-// lane, and the inverse's column j is back substituted by lane j.  Rows and
+// lane, and the inverse's column j is back substituted by lane j.  A row's
+// writes are seen by the other lanes after wave_lds_sync.  Rows and
 // columns are padded with zeros to S, a multiple of 8, so that sums are read 8
 // terms at a time without a remainder; the other waves only copy in and out.
 // s = 10, 21, 32, 42: 9.8, 22, 37 and 59 us, by 256 threads and three barriers
@@ -234,7 +235,7 @@ __global__ __launch_bounds__(kThreads) void k_chol_inv_lds(int s, const double* 
         sR[k * S + t] = t == k ? piv : u;
         sR[t * S + k] = t == k ? piv : u;
       }
-      __builtin_amdgcn_wave_barrier();
+      wave_lds_sync();
     }
     if (fail) {
       if (t == 0) {
@@ -261,7 +262,7 @@ __global__ __launch_bounds__(kThreads) void k_chol_inv_lds(int s, const double* 
         }
         const double q = (t == i ? 1.0 : -acc) / d;
         if (kept && t >= i) sI[i * S + t] = q;
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
       }
       if (t == 0) *flag = 0;
     }
