@@ -74,7 +74,8 @@ struct TileDesc {
 // acc += (lane J of the 16-lane row's a) * x; every lane of the row is active.
 // The no-op covers the wait states between a vector write of the broadcast
 // operand and its DPP read, which the compiler does not see inside the block;
-// volatile keeps the block out of the divergent code around it.
+// volatile keeps the block out of the divergent code around it.  The sums are
+// early-clobber: the first ones are written before the last operands are read.
 template <int J>
 __device__ inline void fmac_row(float (&acc)[4][1], const float (&a)[4], const float (&x)[1]) {
   asm volatile("s_nop 1\n\t"
@@ -82,7 +83,7 @@ __device__ inline void fmac_row(float (&acc)[4][1], const float (&a)[4], const f
       "v_fmac_f32_dpp %1, %5, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f32_dpp %2, %6, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f32_dpp %3, %7, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
-      : "+v"(acc[0][0]), "+v"(acc[1][0]), "+v"(acc[2][0]), "+v"(acc[3][0])
+      : "+&v"(acc[0][0]), "+&v"(acc[1][0]), "+&v"(acc[2][0]), "+&v"(acc[3][0])
       : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(x[0]), "n"(J));
 }
 template <int J>
@@ -96,8 +97,8 @@ __device__ inline void fmac_row(float (&acc)[4][2], const float (&a)[4], const f
       "v_fmac_f32_dpp %5, %10, %13 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f32_dpp %6, %11, %12 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f32_dpp %7, %11, %13 row_newbcast:%14 row_mask:0xf bank_mask:0xf"
-      : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[1][0]), "+v"(acc[1][1]), "+v"(acc[2][0]),
-        "+v"(acc[2][1]), "+v"(acc[3][0]), "+v"(acc[3][1])
+      : "+&v"(acc[0][0]), "+&v"(acc[0][1]), "+&v"(acc[1][0]), "+&v"(acc[1][1]), "+&v"(acc[2][0]),
+        "+&v"(acc[2][1]), "+&v"(acc[3][0]), "+&v"(acc[3][1])
       : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(x[0]), "v"(x[1]), "n"(J));
 }
 template <int J>
@@ -107,7 +108,7 @@ __device__ inline void fmac_row(double (&acc)[4][1], const double (&a)[4], const
       "v_fmac_f64_dpp %1, %5, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f64_dpp %2, %6, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f64_dpp %3, %7, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
-      : "+v"(acc[0][0]), "+v"(acc[1][0]), "+v"(acc[2][0]), "+v"(acc[3][0])
+      : "+&v"(acc[0][0]), "+&v"(acc[1][0]), "+&v"(acc[2][0]), "+&v"(acc[3][0])
       : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(x[0]), "n"(J));
 }
 template <int J>
@@ -121,8 +122,8 @@ __device__ inline void fmac_row(double (&acc)[4][2], const double (&a)[4], const
       "v_fmac_f64_dpp %5, %10, %13 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f64_dpp %6, %11, %12 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
       "v_fmac_f64_dpp %7, %11, %13 row_newbcast:%14 row_mask:0xf bank_mask:0xf"
-      : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[1][0]), "+v"(acc[1][1]), "+v"(acc[2][0]),
-        "+v"(acc[2][1]), "+v"(acc[3][0]), "+v"(acc[3][1])
+      : "+&v"(acc[0][0]), "+&v"(acc[0][1]), "+&v"(acc[1][0]), "+&v"(acc[1][1]), "+&v"(acc[2][0]),
+        "+&v"(acc[2][1]), "+&v"(acc[3][0]), "+&v"(acc[3][1])
       : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(x[0]), "v"(x[1]), "n"(J));
 }
 // lane J of the 16-lane row
