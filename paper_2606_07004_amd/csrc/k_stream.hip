@@ -266,29 +266,32 @@ __device__ inline void spmm_body(int64_t n, int Lr, int lgES_arg, const int* __r
           if (FUSED && c0 == row) xd[c] = x;
         }
     };
-    // entry positions are unsigned: the round past a row that ends at 2^31 - 1,
-    // the largest entry count of a matrix, starts beyond an int
-    const unsigned kbeg = (unsigned)rp[row];
-    const unsigned kend = (unsigned)rp[row + 1];
+    // entry positions less kRound, the most a round takes: the round past a row
+    // that ends at 2^31 - 1, the largest entry count of a matrix, would start
+    // beyond an int (unsigned positions cost two registers, a wave per SIMD in
+    // some instances)
+    constexpr int kRound = 64 * KE;
+    const int kbeg = rp[row] - kRound;
+    const int kend = rp[row + 1] - kRound;
     // the row's L lanes load KE * L consecutive entries (column, value) per
     // round, lane l holding entries l, l + L, ..., and pass them around the
     // group by lane shuffles; entries are accumulated in order
-    for (unsigned base = kbeg; base < kend; base += (unsigned)(rm.L * KE)) {
+    for (int base = kbeg; base < kend; base += rm.L * KE) {
       int myc[KE];
       A mya[KE];
 #pragma unroll
       for (int u = 0; u < KE; ++u) {
-        const unsigned kk = base + (unsigned)(rm.gl + rm.L * u);
+        const int kk = base + rm.gl + rm.L * u;
         myc[u] = row;
         mya[u] = A(0);
         if (kk < kend) {
-          myc[u] = ci[kk];
-          mya[u] = value_as<VT, A>(va[kk]);
+          myc[u] = ci[(int64_t)kk + kRound];
+          mya[u] = value_as<VT, A>(va[(int64_t)kk + kRound]);
         }
       }
 #pragma unroll
       for (int u = 0; u < KE; ++u) {
-        const int cnt = min(rm.L, (int)(kend - base) - rm.L * u);
+        const int cnt = min(rm.L, kend - base - rm.L * u);
         if (cnt <= 0) break;
         if (ES == 1) {
           int j = 0;
