@@ -508,6 +508,13 @@ ld_status ld_debug_stream(ld_ctx* ctx, uint64_t bytes, int32_t reads, int32_t wr
  * of the group, zero where that row has no entry).  Blocking. */
 ld_status ld_debug_row_groups(ld_matrix* a, int64_t* n_union, int32_t* gp, int32_t* col,
                               double* val);
+/* Debug: the kernels that a steady Krylov step of `p`'s estimate block takes on
+ * this matrix, out[8]: the product (0 CSR rows, 1 row groups, 2 row tiles), its
+ * lanes per row and chunks per lane (row tiles set their own), 1 for its
+ * latency instance (few rows), 1 for bands of the matrix's frequent stride, 1
+ * for the update that reads a row ahead of its coefficients; then the matrix's
+ * row tiles (0: none) and the largest union of a tile.  No GPU work. */
+ld_status ld_debug_step_paths(ld_matrix* a, const ld_params* p, int32_t* out);
 
 #ifdef __cplusplus
 }

@@ -1652,6 +1652,14 @@ static bool update_pre(const UpdateItem& it) {
   return it.g.xbytes == 8 || (it.g.C * it.g.vec <= 8 && nchunk <= 24 * kMaxBlocks);
 }
 
+void step_instances(const SpmmItem& p, const UpdateItem& u, int32_t out[3]) {
+  const bool rows = p.g.rg == 0;
+  out[0] = rows && spmm_few(p);
+  // grids are multiples of 8 from 8 blocks up
+  out[1] = rows && !spmm_few(p) && spmm_bands(p.g, 8).c > 0;
+  out[2] = update_pre(u);
+}
+
 template <typename XT, int C, int NV, bool V1, bool SYM, bool PRE = false>
 static hipError_t update_launch(hipStream_t st, UpdateItem* items, const int* idx, int cnt) {
   auto fn = k_update<XT, C, NV, V1, SYM, PRE>;

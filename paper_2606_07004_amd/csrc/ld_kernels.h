@@ -328,6 +328,9 @@ hipError_t launch_spmm_tile_group(hipStream_t st, SpmmItem* items, const int* id
 // rounds of chunks on as many blocks as they need.
 int stream_grid(const Geom& g, const void* fn, bool even = false);
 hipError_t launch_update_batch(hipStream_t st, UpdateItem* items, int count);
+// The instances that the items take: out[0] latency, out[1] bands (product),
+// out[2] the update that reads ahead.
+void step_instances(const SpmmItem& p, const UpdateItem& u, int32_t out[3]);
 hipError_t launch_reduce_batch(hipStream_t st, const ReduceItem* items, int count);
 hipError_t launch_step_finish_batch(hipStream_t st, const FinishItem* items, int count);
 

@@ -1791,6 +1791,24 @@ ld_status Run::tune_set(int spmm_lanes, int spmm_chunks, int spmm_split, int upd
   return LD_OK;
 }
 
+void Run::step_paths(int32_t out[8]) const {
+  const bool ps = presub_choice(ldB_);
+  SpmmItem p{};
+  p.g = krylov_geom(ldB_, 0);
+  p.vt = mixed_ ? a_->vt_lo : VT_F64;
+  p.nf = 1;
+  if (p.g.rg) p.rg = row_groups();
+  UpdateItem u{};
+  u.g = krylov_geom(ldB_, upd_which(ps));
+  u.nv = upd_steady_nv(ps);
+  out[0] = p.g.rg ? (spmm_tile_key(p) ? 2 : 1) : 0;
+  out[1] = p.g.L;
+  out[2] = p.g.C;
+  step_instances(p, u, out + 3);
+  out[6] = a_->tl_col ? (int32_t)a_->tl_shape.ntile : 0;
+  out[7] = a_->tl_col ? a_->tl_umax : 0;
+}
+
 // Host threads for a pass over `work` items: one per ~4M items, at most 16.
 static int host_threads(int64_t work) {
   const int hw = (int)std::max(1u, std::thread::hardware_concurrency());
@@ -2714,6 +2732,15 @@ ld_status ld_debug_row_groups(ld_matrix* a, int64_t* n_union, int32_t* gp, int32
   LD_HIP_API(hipMemcpy(gp, a->rg_gp, ((size_t)ng + 1) * 4, hipMemcpyDeviceToHost));
   LD_HIP_API(hipMemcpy(col, a->rg_col, (size_t)a->rg_nu * 4, hipMemcpyDeviceToHost));
   LD_HIP_API(hipMemcpy(val, a->rg_val64, (size_t)a->rg_nu * kRowGroup * 8, hipMemcpyDeviceToHost));
+  return LD_OK;
+}
+
+ld_status ld_debug_step_paths(ld_matrix* a, const ld_params* p, int32_t* out) {
+  if (!a || !p || !out) return set_error(LD_E_INVALID_ARG, "null argument");
+  Run run(a, *p);
+  const ld_status rc = run.validate();
+  if (rc != LD_OK) return rc;
+  run.step_paths(out);
   return LD_OK;
 }
 

@@ -223,6 +223,7 @@ class Run {
                     hipEvent_t done = nullptr);
   ld_matrix* matrix() const { return a_; }
   const ld_params& params() const { return p_; }
+  void step_paths(int32_t out[8]) const;  // see ld_debug_step_paths
 
  private:
   struct Phase;

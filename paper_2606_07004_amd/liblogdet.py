@@ -158,6 +158,7 @@ _SIGNATURES = [
     ("ld_debug_probes", C.c_int32, [C.c_void_p, C.c_uint64, C.c_int64, C.c_int32, C.c_int32,
                                     C.c_int32, _DP]),
     ("ld_debug_row_groups", C.c_int32, [C.c_void_p, C.POINTER(C.c_int64), _IP, _IP, _DP]),
+    ("ld_debug_step_paths", C.c_int32, [C.c_void_p, C.POINTER(ld_params), _IP]),
 ]
 
 
@@ -437,6 +438,14 @@ def ld_debug_row_groups(a, n: int):
     _check(lib().ld_debug_row_groups(a, C.byref(nu), gp.ctypes.data_as(_IP),
                                      col.ctypes.data_as(_IP), val.ctypes.data_as(_DP)))
     return gp, col, val
+
+
+def ld_debug_step_paths(a, params: ld_params) -> dict:
+    """The kernels that a steady Krylov step of `params` takes on matrix `a`."""
+    out = (C.c_int32 * 8)()
+    _check(lib().ld_debug_step_paths(a, C.byref(params), out))
+    return dict(zip(("product", "lanes", "chunks", "latency", "bands", "update_ahead", "tiles",
+                     "tile_union"), out))
 
 
 class Context:
