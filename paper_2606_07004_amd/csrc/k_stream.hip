@@ -1413,11 +1413,18 @@ static bool spmm_item_ok(const SpmmItem& it) {
   return true;
 }
 
-// One chunk per lane and at most two chunks of rows per resident block: the
-// latency instance (its 6 blocks per CU; the rule depends on the item alone, so
-// a request takes the same instance in every batch).
+// One chunk per lane and at most two chunks of rows per resident block of 6
+// per CU: the latency instance (the rule depends on the item alone, so a request
+// takes the same instance in every batch).  From 4 lanes per row on: its four
+// gathers in flight are four of the entries that the row's lanes hold, and on
+// fewer lanes it only added its registers (1 and 2 lanes, 3000 to 40 000 rows
+// of 9 to 50 entries: 1.02 to 1.07 of the estimate's time).  Not with FP16
+// vectors, whose instance spills (3000 to 190 000 rows of 5 to 7 entries, 12 to
+// 96 probes: 0.98 of the time without it, 1.04 with it just past one chunk per
+// block).  Instances of 4 blocks per CU (FP64 values on FP32 vectors, two fused
+// products) take it as far: 0.82 to 0.98 at 1400 to 3070 chunks.
 static bool spmm_few(const SpmmItem& it) {
-  return it.g.C == 1 && it.g.lges == 0 && !it.g.rg &&
+  return it.g.C == 1 && it.g.L >= 4 && it.g.xbytes >= 4 && it.g.lges == 0 && !it.g.rg &&
          (it.g.n + rows_per_block(it.g.L) - 1) / rows_per_block(it.g.L) <= 2 * 6 * 256;
 }
 
@@ -1485,8 +1492,9 @@ static hipError_t spmm_launch_c(hipStream_t st, int C, SpmmItem* items, const in
     if (C == 2) return spmm_launch<VT, XT, 2, NF, true>(st, items, idx, cnt);
     return hipErrorInvalidValue;
   }
-  if (spmm_few(items[idx[0]]))
-    return spmm_launch<VT, XT, 1, NF, false, true>(st, items, idx, cnt);
+  if constexpr (sizeof(XT) >= 4)
+    if (spmm_few(items[idx[0]]))
+      return spmm_launch<VT, XT, 1, NF, false, true>(st, items, idx, cnt);
   LD_DISPATCH_C(C, { e = spmm_launch<VT, XT, CC, NF, false>(st, items, idx, cnt); });
   return e;
 }

@@ -74,3 +74,17 @@ def test_products(L, ctx):
     wide = W.wendland_grid(40, 50, 24.0, nugget=0.5)
     got = _paths(L, ctx, wide, 30, lo=0.5)
     assert got["product"] == 1 and got["tiles"] == 0
+
+
+# rows of 8 chunks (30 FP32 probes): 32 rows a chunk of rows; 4, 2 and 1 chunks
+# of a row: 64, 128 and 256
+@pytest.mark.parametrize("n,npr,prec,vt,k,latency", [
+    (32 * 3072, 30, "mixed", "fp32", 2, 1), (32 * 3072 + 1, 30, "mixed", "fp32", 2, 0),
+    (32 * 3072, 30, "mixed", "fp64", 2, 1), (16 * 3072, 30, "fp64", "fp64", 10, 1),
+    (20000, 16, "mixed", "fp32", 2, 1), (20000, 8, "mixed", "fp32", 2, 0),
+    (20000, 4, "mixed", "fp64", 2, 0), (20000, 4, "fp64", "fp64", 2, 0),
+    (20000, 8, "fp64", "fp64", 2, 1), (20000, 64, "half", "fp32", 2, 0),
+])
+def test_latency_instance(L, ctx, n, npr, prec, vt, k, latency):
+    got = _paths(L, ctx, _stripes(n, (1, 37)), npr, prec, vt, k)
+    assert got["product"] == 0 and got["latency"] == latency
