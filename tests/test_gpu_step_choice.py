@@ -88,3 +88,20 @@ def test_products(L, ctx):
 def test_latency_instance(L, ctx, n, npr, prec, vt, k, latency):
     got = _paths(L, ctx, _stripes(n, (1, 37)), npr, prec, vt, k)
     assert got["product"] == 0 and got["latency"] == latency
+
+
+# the update that reads a row ahead: rows of less than a line (7 chunks and
+# fewer) up to 320 chunks of rows, FP16 ones past 1024 again; wider rows up to 24
+# (12) rounds of 2048 chunks
+@pytest.mark.parametrize("n,npr,prec,k,ahead", [
+    (256 * 320, 4, "mixed", 2, 1), (256 * 320 + 1, 4, "mixed", 2, 0),
+    (32 * 320, 28, "mixed", 2, 1), (32 * 320 + 1, 28, "mixed", 2, 0),
+    (32 * 320 + 1, 30, "mixed", 2, 1), (256 * 320 + 1, 2, "fp64", 2, 0),
+    (128 * 320, 4, "fp64", 3, 1), (128 * 320 + 1, 4, "fp64", 3, 0), (64 * 320 + 1, 8, "fp64", 3, 1),
+    (64 * 320 + 1, 30, "half", 2, 0), (64 * 1024 + 1, 30, "half", 2, 1),
+    (16 * 24 * 2048, 64, "mixed", 2, 1), (16 * 24 * 2048 + 1, 64, "mixed", 2, 0),
+    (16 * 12 * 2048, 30, "fp64", 4, 1), (16 * 12 * 2048 + 1, 30, "fp64", 4, 0),
+    (16 * 12 * 2048 + 1, 30, "fp64", 2, 1), (3000, 30, "mixed", 6, 0),
+])
+def test_update_ahead(L, ctx, n, npr, prec, k, ahead):
+    assert _paths(L, ctx, _stripes(n, (1,)), npr, prec, k=k)["update_ahead"] == ahead
