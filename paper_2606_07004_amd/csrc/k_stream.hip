@@ -709,8 +709,8 @@ template <typename XT, int C, int V1E = C * V16<XT>::N>
 constexpr int update_min_blocks(bool v1) {
   return !v1 ? 4 : (V1E > 24 ? 1 : (V1E > 12 ? 2 : (V1E > 8 ? 3 : 4)));
 }
-// PRE (one vector: window 2): a row's loads come before the first round's
-// coefficients, whose latency they then share.
+// PRE (up to 4 vectors, update_pre): a row's loads come before the first
+// round's coefficients, whose latency they then share.
 template <typename XT, int C, int NV, bool V1, bool SYM, bool PRE>
 __global__ __launch_bounds__(kThreads, (update_min_blocks<XT, C>(V1))) void k_update(
     BatchArgs<UpdDesc> bt) {
@@ -1718,7 +1718,11 @@ static hipError_t update_launch_c(hipStream_t st, int C, UpdateItem* items, cons
   hipError_t e = hipErrorInvalidValue;
   if constexpr (NV <= 4 && !V1 && (NV == 1 || sizeof(XT) >= 4)) {
     if (update_pre(items[idx[0]])) {
-      LD_DISPATCH_C(C, { e = update_launch<XT, CC, NV, V1, SYM, true>(st, items, idx, cnt); });
+      // the chunks per lane that update_pre admits
+      constexpr int MC = NV > 1 ? 1 : (sizeof(XT) == 8 ? kMaxC : 8 / V16<XT>::N);
+      LD_DISPATCH_C(C, {
+        if constexpr (CC <= MC) e = update_launch<XT, CC, NV, V1, SYM, true>(st, items, idx, cnt);
+      });
       return e;
     }
   }
