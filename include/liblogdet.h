@@ -308,15 +308,18 @@ ld_status ld_request_bytes(ld_matrix* a, const ld_params* p, uint64_t* bytes);
  * default on such matrices for blocks of 16 columns or more where values
  * and vectors have the same type, with one chunk per lane for FP32 and two
  * for FP64, and ld_autotune tries it in every plain geometry of at most 2
- * chunks per lane.  Blocks of 16 columns or more take the row groups in tiles
- * of 16 whose probe rows are gathered once into LDS, where every tile's union
- * of columns fits; the lanes and chunks then do not change the product, and
- * ld_autotune tries it in both chunk mappings.  A row's sum sees its
+ * chunks per lane.  In that default geometry (as many lanes as chunks of 16
+ * bytes, FP64 half as many with two chunks each) blocks of 16 columns or more
+ * take the row groups in tiles of 16 whose probe rows are gathered once into
+ * LDS, where every tile's union of columns fits; the tiles set their own
+ * lanes, and any other geometry takes the row-group product.  ld_autotune
+ * tries both, in both chunk mappings.  A row's sum sees its
  * nonzero terms in CSR order, so the product's output is the CSR product's.
  * The groups are built on the device when the matrix is created.
  * ld_autotune times every such (L, C, E) with L a power of two and at most
  * half a row of idle chunks on this matrix, and L = ceil(chunks / C) where
- * that is not a power of two, for the probe-block shapes and
+ * that is not a power of two, and the untuned geometries, for the
+ * probe-block shapes and
  * precision that `p` implies (the estimate block and, for OSA-IOP and So-SLQ,
  * the sketch-run block), each kernel `reps` times per round over three
  * rounds, keeping the fastest per kernel.  Both are timed as a steady-state
@@ -370,10 +373,10 @@ ld_status ld_autotune(ld_matrix* a, const ld_params* p, int32_t reps, ld_tune_re
  * the window class of `p`), with the step schedule step_presub (1: the
  * product subtracts the second-newest window vector, the default; 0: the
  * update subtracts the whole window; see ld_tune_result), and the product
- * over the matrix's row groups (spmm_row_groups 1: FP32 or FP64 Krylov
- * vectors on a matrix that keeps them, not BF16 values, C <= 2, no entry
- * split, no row tiles) or its CSR
- * rows (0).  Any (L, C, E) with L <= 64, 1 <= C <= 4, E in {1, 2, 4, 8},
+ * over the matrix's row groups (spmm_row_groups 1, in tiles of 16 groups
+ * where L and C are their default: FP32 or FP64 Krylov vectors on a matrix
+ * that keeps them, not BF16 values, C <= 2, no entry split, no row stride) or
+ * its CSR rows (0).  Any (L, C, E) with L <= 64, 1 <= C <= 4, E in {1, 2, 4, 8},
  * E <= L, C <= 2 when E > 1, and (L / E) * C chunks covering the block is
  * accepted, where L is a power of two when E > 1; anything else is
  * LD_E_INVALID_ARG and stores nothing. */
@@ -509,11 +512,11 @@ ld_status ld_debug_stream(ld_ctx* ctx, uint64_t bytes, int32_t reads, int32_t wr
 ld_status ld_debug_row_groups(ld_matrix* a, int64_t* n_union, int32_t* gp, int32_t* col,
                               double* val);
 /* Debug: the kernels that a steady Krylov step of `p`'s estimate block takes on
- * this matrix, out[8]: the product (0 CSR rows, 1 row groups, 2 row tiles), its
- * lanes per row and chunks per lane (row tiles set their own), 1 for its
+ * this matrix, out[8]: the product (0 CSR rows, 1 row groups, 2 their tiles), its
+ * lanes per row and chunks per lane (tiles set their own), 1 for its
  * latency instance (few rows), 1 for bands of the matrix's frequent stride, 1
  * for the update that reads a row ahead of its coefficients; then the matrix's
- * row tiles (0: none) and the largest union of a tile.  No GPU work. */
+ * tiles of row groups (0: none) and the largest union of a tile.  No GPU work. */
 ld_status ld_debug_step_paths(ld_matrix* a, const ld_params* p, int32_t* out);
 
 #ifdef __cplusplus

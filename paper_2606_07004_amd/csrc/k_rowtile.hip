@@ -480,7 +480,7 @@ static int tile_class(const SpmmItem& it) {
 }
 
 int spmm_tile_key(const SpmmItem& it) {
-  if (!it.g.rg || !it.rg.tile.tcol || it.g.ld < kTileMinCols) return 0;
+  if (it.g.rg != 2 || !it.rg.tile.tcol || it.g.ld < kTileMinCols) return 0;
   const int c = tile_class(it);
   return c < 0 ? 0 : 1 + c + 8 * tile_cpl(it.g.ld, it.g.xbytes);
 }

@@ -1137,7 +1137,8 @@ static bool geom_ok(const Geom& g) {
          (g.L >> g.lges) * g.C >= g.ncolv && g.nblk >= 1 && (int64_t)g.nblk * g.rpb >= g.n &&
          g.ts >= 0 && g.ts <= kMaxRowStride &&
          (g.ts == 0 || ((1 << g.lgL) == g.L && g.ts % (64 / g.L) == 0)) &&
-         (g.rg == 0 || (g.rg == 1 && g.lges == 0 && g.ts == 0 && g.C <= 2 && g.xbytes >= 4));
+         (g.rg == 0 ||
+          ((g.rg == 1 || g.rg == 2) && g.lges == 0 && g.ts == 0 && g.C <= 2 && g.xbytes >= 4));
 }
 
 // Resident 256-thread blocks of a kernel on the whole device (cached).
@@ -1515,7 +1516,7 @@ hipError_t launch_spmm_batch(hipStream_t st, SpmmItem* items, int count) {
     const int tk = spmm_tile_key(it);  // a tile item's lanes and chunks are its own
     return (uint64_t)it.g.xbytes | ((uint64_t)it.vt << 8) | ((uint64_t)(tk ? 0 : it.g.C) << 16) |
            ((uint64_t)it.nf << 24) | ((uint64_t)(it.g.lges > 0) << 32) |
-           ((uint64_t)it.g.rg << 33) | ((uint64_t)spmm_few(it) << 34) | ((uint64_t)tk << 40);
+           ((uint64_t)(it.g.rg != 0) << 33) | ((uint64_t)spmm_few(it) << 34) | ((uint64_t)tk << 40);
   };
   return launch_grouped(items, count, key, [&](const int* idx, int cnt) -> hipError_t {
     const SpmmItem& it = items[idx[0]];

@@ -50,7 +50,7 @@ struct Geom {
   int band = 0;    // product only: 0, or a frequent stride P of the matrix (BandMap); used
                    // with xil = ts = lges = rg = 0
   int rg = 0;      // product only: 1 = the matrix's row groups (RowGroups below)
-                   // instead of its CSR rows; FP32 values on FP32 vectors or
+                   // instead of its CSR rows, 2 = in row tiles; FP32 values on FP32 vectors or
                    // FP64 values on FP64 or FP32 vectors, C <= 2, no entry
                    // split, no row tiles
 };
@@ -318,9 +318,8 @@ hipError_t launch_spmm_batch(hipStream_t st, SpmmItem* items, int count);
 // The row-group items of a batch (g.rg, checked by launch_spmm_batch), at
 // most kMaxBatch of them with the same C and nf: one launch.
 hipError_t launch_spmm_rg_group(hipStream_t st, SpmmItem* items, const int* idx, int cnt);
-// Non-zero where a row-group item takes the row-tile product (its matrix
-// keeps tiles and the block has at least 16 columns): items of one launch
-// share the key.
+// Non-zero where an item takes the row-tile product (g.rg = 2, on a matrix
+// that keeps tiles, of at least 16 columns): items of one launch share the key.
 int spmm_tile_key(const SpmmItem& it);
 hipError_t launch_spmm_tile_group(hipStream_t st, SpmmItem* items, const int* idx, int cnt);
 // Grid of a streaming kernel `fn` over g's rows (row groups with g.rg): at

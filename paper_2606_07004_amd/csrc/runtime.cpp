@@ -469,8 +469,23 @@ bool Run::presub_choice(int ld) const {
   return it == a_->tune.end() || it->second.first == 0;
 }
 
-Geom Run::with_band(Geom g) const {
+// Lanes and chunks per lane of the row groups by default: one chunk per lane
+// with FP32 vectors, two with FP64 ones (the 64-probe covariance: 16 x 2 0.55 ms,
+// 32 x 1 0.67 ms per product).
+static std::pair<int, int> rowgroup_default(int ld, int xbytes) {
+  const int ncolv = ld / (16 / xbytes);
+  const int C = (xbytes == 8 && ncolv >= 4) ? 2 : 1;
+  return {(ncolv + C - 1) / C, C};
+}
+
+// Row tiles set their own lanes, so they are what the row groups' default
+// geometry stands for where the matrix keeps them; any other lanes and chunks
+// take the row-group product.
+Geom Run::product_geom(Geom g) const {
   g.band = a_->band;
+  if (g.rg && a_->tl_col && g.ld >= kTileMinCols &&
+      std::make_pair(g.L, g.C) == rowgroup_default(g.ld, g.xbytes))
+    g.rg = 2;
   return g;
 }
 
@@ -485,24 +500,26 @@ Geom Run::krylov_geom(int ld, int which) const {
       g.xil = (it->second.first >> 12) & 1;    // chunk mapping of the product
       g.ts = (it->second.first >> 16) & 0x7fff;  // row tiles of the product
       g.rg = (it->second.first >> 13) & 1;       // row groups of the product
-      if (geom_usable(g) && (g.rg == 0 || rg_ok())) return which == 0 ? with_band(g) : g;
+      if (geom_usable(g) && (g.rg == 0 || rg_ok())) return which == 0 ? product_geom(g) : g;
     }
   }
+  return default_geom(ld, which);
+}
+
+// The untuned geometry.
+Geom Run::default_geom(int ld, int which) const {
   if (which == 0 && rg_ok() && ld >= 16 && (!(mixed_ && a_->vt_lo == VT_F64) || a_->tl_col)) {
     // row groups (blocks of 16 columns or more: on narrower ones the groups'
-    // extra multiply-adds and shuffles weigh more than the gathers they
-    // save): one chunk per lane with FP32 vectors, two with FP64 ones (the
-    // 64-probe covariance: 16 x 2 0.55 ms, 32 x 1 0.67 ms per product).
+    // extra multiply-adds and shuffles weigh more than the gathers they save).
     // FP64 values on FP32 vectors take them only where the matrix keeps row
     // tiles (estimates, tiles against the CSR product: scattered covariances of
     // 3K to 200K rows, 16 to 96 probes, 0.63 to 0.99 of the time, grid ones 0.56
     // to 0.90); the row-group product's FP64 sums of 4 rows cost it occupancy
     // (22.3 against 21.3 ms), but the autotuner and ld_tune_set can still take it
-    const int ncolv = ld / (16 / xb_);
-    const int C = (xb_ == 8 && ncolv >= 4) ? 2 : 1;
-    Geom g = make_geom_lc(n_, ld, xb_, (ncolv + C - 1) / C, C);
+    const auto lc = rowgroup_default(ld, xb_);
+    Geom g = make_geom_lc(n_, ld, xb_, lc.first, lc.second);
     g.rg = 1;
-    if ((ncolv + C - 1) / C <= 64 && geom_usable(g)) return g;
+    if (lc.first <= 64 && geom_usable(g)) return product_geom(g);
   }
   if (which == 0 && a_->nnz >= 64 * a_->n) {
     // long rows: one chunk per lane and the row's entries over two lane
@@ -523,7 +540,7 @@ Geom Run::krylov_geom(int ld, int which) const {
     // wave busy than the power of two above it (96 probes: 5 rows of 12
     // lanes per wave instead of 4 of 16 with 4 idle)
     Geom g = make_geom_lc(n_, ld, xb_, d.ncolv, 1);
-    if (geom_usable(g)) return with_band(g);
+    if (geom_usable(g)) return product_geom(g);
   }
   // Blocks of less than 24 chunks that make_geom gives several chunks per lane:
   // a load of L < 8 lanes takes less than a 128-byte line of a row, and rows
@@ -543,7 +560,7 @@ Geom Run::krylov_geom(int ld, int which) const {
     if (which == 0) {
       const Geom g = d.ncolv < 22 ? make_geom_lc(n_, ld, xb_, d.ncolv, 1)
                                   : make_geom_lc(n_, ld, xb_, L / 2, 2);
-      if (geom_usable(g)) return with_band(g);
+      if (geom_usable(g)) return product_geom(g);
     } else if (d.L < 4 || n_ * L > 2048 * kThreads) {
       const Geom g = make_geom_lc(n_, ld, xb_, L, 1);
       if (geom_usable(g)) return g;
@@ -558,9 +575,9 @@ Geom Run::krylov_geom(int ld, int which) const {
   if (which == 0 && xb_ != 2 && d.C == 1 && (d.ncolv >= 52 || (d.ncolv == 32 && xb_ == 8)) &&
       n_ * d.L > 10 * 1024 * kThreads) {
     const Geom g = make_geom_lc(n_, ld, xb_, d.L / 2, 2);
-    if (geom_usable(g)) return with_band(g);
+    if (geom_usable(g)) return product_geom(g);
   }
-  return which == 0 ? with_band(d) : d;
+  return which == 0 ? product_geom(d) : d;
 }
 
 // One layout for measuring and for carving: with base == nullptr only the
@@ -1556,21 +1573,36 @@ ld_status Run::tune(hipStream_t st, int reps, ld_tune_result* out) {
     // entry splits only pay on rows of many entries
     auto cand = tune_candidates(n_, ld, xb_, a_->nnz >= 16 * a_->n, true,
                                 stride_candidates(st));
+    auto index_of = [&](const std::pair<int, int>& c) -> int {
+      const auto it = std::find(cand.begin(), cand.end(), c);
+      if (it != cand.end()) return (int)(it - cand.begin());
+      cand.push_back(c);
+      return (int)cand.size() - 1;
+    };
     if (rg_ok()) {
-      // the row-group product in every plain geometry of at most two chunks
-      // per lane (both chunk mappings), and its default first among them
+      // the row groups in their default geometry (row tiles, where the matrix
+      // keeps them) and in every plain geometry of at most two chunks per lane,
+      // both chunk mappings
       const size_t base = cand.size();
+      const auto d = rowgroup_default(ld, xb_);
       const int ncolv = ld / (16 / xb_);
-      if (ncolv <= 64) cand.push_back({ncolv | (1 << 13), 1});
-      if (a_->tl_col && ld >= kTileMinCols) {
-        // the row-tile product sets its own lanes: the other chunk mapping only
-        if (ncolv <= 64) cand.push_back({ncolv | (1 << 12) | (1 << 13), 1});
-      } else for (size_t i = 0; i < base; ++i) {
+      if (d.first <= 64) {
+        index_of({d.first | (1 << 13), d.second});
+        index_of({d.first | (1 << 12) | (1 << 13), d.second});
+      }
+      if (ncolv <= 64) index_of({ncolv | (1 << 13), 1});
+      for (size_t i = 0; i < base; ++i) {
         const Geom g = candidate_geom(n_, ld, xb_, cand[i]);
-        if (g.lges == 0 && g.ts == 0 && g.C <= 2 && !(g.L == ncolv && g.C == 1 && g.xil == 0))
-          cand.push_back({cand[i].first | (1 << 13), cand[i].second});
+        if (g.lges == 0 && g.ts == 0 && g.C <= 2)
+          index_of({cand[i].first | (1 << 13), cand[i].second});
       }
     }
+    // the untuned geometries, which a choice has to beat
+    const Geom gp0 = default_geom(ld, 0), gu0 = default_geom(ld, upd_which(true));
+    const int dp = index_of({gp0.L | (gp0.lges << 8) | (gp0.xil << 12) | ((gp0.rg != 0) << 13) |
+                                 (gp0.ts << 16),
+                             gp0.C});
+    const int du = index_of({gu0.L, gu0.C});
     const RowGroups rgs = row_groups();
     const int nc = (int)cand.size();
     std::vector<double> tp(nc, 1e300), tu(nc, 1e300);
@@ -1584,7 +1616,7 @@ ld_status Run::tune(hipStream_t st, int reps, ld_tune_result* out) {
     }
     for (int round = 0; round < 3; ++round)
       for (int c = 0; c < nc; ++c) {
-        const Geom g = with_band(candidate_geom(n_, ld, xb_, cand[c]));
+        const Geom g = product_geom(candidate_geom(n_, ld, xb_, cand[c]));
         int nb = 0;
         float ms = 0.f;
         auto product = [&]() {
@@ -1617,8 +1649,8 @@ ld_status Run::tune(hipStream_t st, int reps, ld_tune_result* out) {
     // (timing noise would otherwise pick geometries at random, and the
     // update's geometry also serves the wider OSA-IOP v1 pass, which the
     // tuner does not time)
-    int bp = 0, bu = 0;
-    for (int c = 1; c < nc; ++c) {
+    int bp = dp, bu = du;
+    for (int c = 0; c < nc; ++c) {
       if (tp[c] < 0.99 * tp[bp]) bp = c;
       if (tu[c] < 0.99 * tu[bu]) bu = c;
     }
@@ -1637,11 +1669,11 @@ ld_status Run::tune(hipStream_t st, int reps, ld_tune_result* out) {
         vun.x[v] = v + 1 == nvn ? X : V;
         vun.mult[v] = mult;
       }
-      const Geom gp = with_band(candidate_geom(n_, ld, xb_, cand[bp]));
+      const Geom gp = product_geom(candidate_geom(n_, ld, xb_, cand[bp]));
       const Geom gu = candidate_geom(n_, ld, xb_, cand[bu]);
       std::vector<int> ucand;
       for (int c = 0; c < nc; ++c) {
-        const Geom g = with_band(candidate_geom(n_, ld, xb_, cand[c]));
+        const Geom g = product_geom(candidate_geom(n_, ld, xb_, cand[c]));
         if (g.lges == 0 && g.xil == 0 && g.ts == 0 && g.rg == 0) ucand.push_back(c);
       }
       double t_psp = 1e300, t_psu = 1e300, t_pp = 1e300;
@@ -1673,14 +1705,14 @@ ld_status Run::tune(hipStream_t st, int reps, ld_tune_result* out) {
                                &nb, nv);
         }, t_psu));
         for (int c : ucand) {
-          const Geom g = with_band(candidate_geom(n_, ld, xb_, cand[c]));
+          const Geom g = product_geom(candidate_geom(n_, ld, xb_, cand[c]));
           LD_HIP(timed([&]() {
             return launch_update(st, g, W, vun, nvn, dcoef, 0, 1, nullptr, nullptr, true, part,
                                  &nb);
           }, t_pu[c]));
         }
       }
-      bun = ucand.front();
+      bun = du;
       for (int c : ucand)
         if (t_pu[c] < 0.99 * t_pu[bun]) bun = c;
       ps_ms = t_psp + t_psu;
@@ -1700,7 +1732,7 @@ ld_status Run::tune(hipStream_t st, int reps, ld_tune_result* out) {
       std::vector<double> tv(nc, 1e300);
       for (int round = 0; round < 3; ++round)
         for (int c = 0; c < nc; ++c) {
-          const Geom g = with_band(candidate_geom(n_, ld, xb_, cand[c]));
+          const Geom g = product_geom(candidate_geom(n_, ld, xb_, cand[c]));
           if (g.lges != 0 || g.xil != 0 || g.ts != 0 || g.rg != 0) continue;
           int nb = 0;
           auto upd = [&]() {
@@ -1716,8 +1748,8 @@ ld_status Run::tune(hipStream_t st, int reps, ld_tune_result* out) {
           LD_HIP(hipEventElapsedTime(&ms, ev.a, ev.b));
           tv[c] = std::min(tv[c], (double)ms / reps);
         }
-      bv = 0;
-      for (int c = 1; c < nc; ++c)
+      bv = du;
+      for (int c = 0; c < nc; ++c)
         if (tv[c] < 0.99 * tv[bv]) bv = c;
     }
     {
@@ -1744,9 +1776,9 @@ ld_status Run::tune(hipStream_t st, int reps, ld_tune_result* out) {
       out->update_lanes = cand[presub ? bu : bun].first;
       out->update_chunks = cand[presub ? bu : bun].second;
       out->spmm_ms = tp[bp];
-      out->spmm_default_ms = tp[0];
+      out->spmm_default_ms = tp[dp];
       out->update_ms = tu[bu];
-      out->update_default_ms = tu[0];
+      out->update_default_ms = tu[du];
       out->candidates = nc;
       out->step_presub = presub ? 1 : 0;
       out->step_presub_ms = ps_ms;

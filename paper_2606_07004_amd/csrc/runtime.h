@@ -241,7 +241,10 @@ class Run {
   // product (which = 0) or update (which = 1) geometry of a Krylov block of
   // width ld: the matrix's tuned choice when it holds one, else the default
   Geom krylov_geom(int ld, int which) const;
-  Geom with_band(Geom g) const;   // a product geometry with the matrix's frequent stride
+  Geom default_geom(int ld, int which) const;
+  // a product geometry as it runs on this matrix: its frequent stride, and row
+  // tiles for row groups in their default geometry
+  Geom product_geom(Geom g) const;
   bool rg_ok() const;             // the product may read the matrix's row groups
   RowGroups row_groups() const;
   int upd_steady_nv(bool presub) const;  // update vectors of a steady-state step

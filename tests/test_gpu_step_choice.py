@@ -105,3 +105,69 @@ def test_latency_instance(L, ctx, n, npr, prec, vt, k, latency):
 ])
 def test_update_ahead(L, ctx, n, npr, prec, k, ahead):
     assert _paths(L, ctx, _stripes(n, (1,)), npr, prec, k=k)["update_ahead"] == ahead
+
+
+# row groups in their default geometry (one chunk per lane, FP64 vectors two) are
+# the row tiles, other lanes and chunks the row-group product; per-probe values
+# against the CSR product in the same step schedule: each row's sum is the same
+# chain of multiply-adds, the fused FP64 inner products differ by their order, and
+# FP32 vectors by single roundings of 2^-24 after them
+@pytest.mark.parametrize("npr,prec,vt,k,lanes,chunks,product", [
+    (30, "mixed", "fp32", 2, 8, 1, 2), (30, "mixed", "fp32", 2, 4, 2, 1),
+    (30, "mixed", "fp32", 2, 16, 1, 1), (22, "mixed", "fp32", 12, 3, 2, 1),
+    (30, "fp64", "fp64", 2, 8, 2, 2), (30, "fp64", "fp64", 12, 8, 2, 2),
+    (37, "fp64", "fp32", 4, 10, 2, 2), (30, "fp64", "fp64", 2, 16, 1, 1),
+    (16, "mixed", "fp64", 2, 4, 1, 2), (16, "mixed", "fp64", 12, 4, 1, 2),
+    (13, "mixed", "fp64", 3, 2, 2, 1), (12, "mixed", "fp32", 2, 3, 1, 1),
+])
+@pytest.mark.parametrize("il", [0, 1])
+def test_row_group_choices(L, ctx, npr, prec, vt, k, lanes, chunks, product, il):
+    a = W.wendland(3001, 48.0, NUG, seed=5)
+    h = ctx.matrix(a, vt=L.LD_VT_FP64 if vt == "fp64" else L.LD_VT_FP32, lo_hint=NUG)
+    try:
+        p = L.make_params(npr, 4, 14, k, 7,
+                          precision=L.LD_PREC_FP64 if prec == "fp64" else L.LD_PREC_MIXED)
+        print(f"\n[case] row groups pinned: probes {npr} {prec} values {vt} window {k} "
+              f"{lanes} x {chunks} interleave {il}", flush=True)
+        K = []
+        for rg in (0, 1):
+            L.ld_tune_set(h, p, lanes, chunks, lanes, chunks, 1, il, 0, 1, rg)
+            got = L.ld_debug_step_paths(h, p)
+            assert (got["product"], got["lanes"], got["chunks"]) == (product if rg else 0, lanes,
+                                                                     chunks)
+            K.append(L.ld_estimate_detail(h, p)[1]["probe_K"])
+            assert np.array_equal(L.ld_estimate_detail(h, p)[1]["probe_K"], K[-1])
+    finally:
+        ctx.release(h)
+    assert np.abs(K[1] - K[0]).max() <= (1e-10 if prec == "fp64" else 1e-6) * np.abs(K[0]).max()
+
+
+# the tuner times the untuned geometries and reports their times: an untuned
+# choice that its list lacked (5 chunks of an update: 8 lanes) or that came last
+# (tiles, against the CSR rows' time) made a tuned matrix slower than an untuned
+@pytest.mark.parametrize("npr,prec,vt", [(20, "mixed", "fp32"), (100, "fp64", "fp64"),
+                                         (128, "fp64", "fp64"), (18, "mixed", "bf16")])
+def test_tuner_times_the_default(L, ctx, npr, prec, vt):
+    a = W.wendland(20011, 48.0, NUG, seed=5)
+    h = ctx.matrix(a, vt={"fp64": L.LD_VT_FP64, "fp32": L.LD_VT_FP32, "bf16": L.LD_VT_BF16}[vt],
+                   lo_hint=NUG)
+    try:
+        p = L.make_params(npr, 4, 14, 2, 7,
+                          precision=L.LD_PREC_FP64 if prec == "fp64" else L.LD_PREC_MIXED)
+        untuned = L.ld_debug_step_paths(h, p)
+        print(f"\n[case] tuner probes {npr} {prec} values {vt} untuned {untuned}", flush=True)
+        tr = L.ld_autotune(h, p, 5)
+        tuned = L.ld_debug_step_paths(h, p)
+        print("  ", tr.as_dict(), tuned, flush=True)
+        # the tile product is far ahead of every other one here (0.6 of the CSR
+        # product's time and less), so the tuner has to find it
+        assert untuned["product"] == tuned["product"] == (0 if vt == "bf16" else 2)
+        assert tr.spmm_ms <= tr.spmm_default_ms and tr.update_ms <= tr.update_default_ms
+        assert tr.spmm_row_groups == (0 if vt == "bf16" else 1)
+        # what the tuner reports can be set again
+        L.ld_tune_set(h, p, tr.spmm_lanes, tr.spmm_chunks, tr.update_lanes, tr.update_chunks,
+                      tr.spmm_entry_split, tr.spmm_interleave, tr.spmm_row_stride, tr.step_presub,
+                      tr.spmm_row_groups)
+        assert L.ld_debug_step_paths(h, p) == tuned
+    finally:
+        ctx.release(h)
