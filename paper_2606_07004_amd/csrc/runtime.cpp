@@ -12,6 +12,7 @@
 // quadratic forms.
 #include "runtime.h"
 #include "serve.h"
+#include "tile_sample.h"
 
 #include <algorithm>
 #include <chrono>
@@ -2101,54 +2102,6 @@ static int64_t group_union_size(const int32_t* rp, const int32_t* ci, int64_t n,
     ++cnt;
   }
   return cnt;
-}
-
-// Distinct columns of a sample of tiles of the given shape, per tile.
-static double sampled_tile_union(int64_t n, const int32_t* rp, const int32_t* ci,
-                                 const TileShape& s) {
-  const int64_t ng = (n + kRowGroup - 1) / kRowGroup;
-  const int ns = (int)std::min<int64_t>(s.ntile, 8);
-  std::vector<int32_t> cols;
-  int64_t total = 0;
-  for (int i = 0; i < ns; ++i) {
-    cols.clear();
-    const int64_t tile = (2 * i + 1) * s.ntile / (2 * ns);
-    for (int k = 0; k < kTileGroups; ++k) {
-      const int64_t g = tile_group(s, ng, tile, k);
-      if (g < 0) continue;
-      const int64_t r0 = g * kRowGroup, r1 = std::min(n, r0 + kRowGroup);
-      cols.insert(cols.end(), ci + rp[r0], ci + rp[r1]);
-    }
-    std::sort(cols.begin(), cols.end());
-    total += std::unique(cols.begin(), cols.end()) - cols.begin();
-  }
-  return ns > 0 ? (double)total / ns : 0.0;
-}
-
-// The tile shape: consecutive groups, or (a grid's rows in natural order) 4
-// groups on each of 4 lines where a sample of tiles then has a smaller union.
-// The line stride is the offset from a middle row to the centre of its next
-// run of consecutive columns.
-static TileShape choose_tile_shape(int64_t n, const int32_t* rp, const int32_t* ci) {
-  TileShape best = make_tile_shape(n, 0, 0);
-  const int64_t row = n / 2;
-  int32_t k = rp[row];
-  const int32_t end = rp[row + 1];
-  while (k < end && ci[k] <= row) ++k;
-  while (k < end && ci[k] == ci[k - 1] + 1) ++k;  // the diagonal's run (the diagonal is present)
-  if (k < end) {
-    int32_t q = k;
-    while (q + 1 < end && ci[q + 1] == ci[q] + 1) ++q;
-    const int64_t stride = ((int64_t)ci[k] + ci[q]) / 2 - row;
-    const int64_t sg = (stride + kRowGroup / 2) / kRowGroup;
-    if (sg >= 4) {
-      const TileShape s = make_tile_shape(n, sg, 4);
-      if (s.sg > 0 &&
-          sampled_tile_union(n, rp, ci, s) < sampled_tile_union(n, rp, ci, best))
-        best = s;
-    }
-  }
-  return best;
 }
 
 // No memory for the tiles: the matrix goes on without them (the groups then
