@@ -461,22 +461,33 @@ __global__ __launch_bounds__(kThreads, 3) void k_spmm_tile(BatchArgs<TileDesc> b
 // 16 columns.
 static int tile_cpl(int ld, int xbytes) { return xbytes == 4 && ld > kTileLanes ? 2 : 1; }
 
-static size_t tile_lds(const SpmmItem& it) {
-  const size_t pb = (size_t)kTileLanes * tile_cpl(it.g.ld, it.g.xbytes) * it.g.xbytes;
+static size_t tile_lds(int rows, int ld, int xbytes) {
+  const size_t pb = (size_t)kTileLanes * tile_cpl(ld, xbytes) * xbytes;
   const size_t red = (size_t)kThreads * 2 * sizeof(double);
   // the load phase writes whole waves' rows: up to 1024 bytes past the union
-  return std::max(red, (size_t)it.rg.tile.umax * pb + 1024);
+  return std::max(red, (size_t)rows * pb + 1024);
 }
 
 // LDS classes by the blocks a CU holds (4, 3, 2 or 1 of its 128 pieces of 1280
 // bytes): requests of one launch share a class, so the launch's LDS (the
 // class's bound) and a request's grid do not depend on what it is batched with.
 constexpr size_t kTileLdsClass[] = {32 * 1280, 42 * 1280, 64 * 1280, 128 * 1280};
-static int tile_class(const SpmmItem& it) {
-  const size_t need = tile_lds(it);
+static int tile_class(int rows, int ld, int xbytes) {
+  const size_t need = tile_lds(rows, ld, xbytes);
   for (int c = 0; c < 4; ++c)
     if (need <= kTileLdsClass[c]) return c;
   return -1;
+}
+static int tile_class(const SpmmItem& it) {
+  return tile_class(it.rg.tile.umax, it.g.ld, it.g.xbytes);
+}
+int tile_blocks(int rows, int ld, int xbytes) {
+  const int c = tile_class(rows, ld, xbytes);
+  return c < 0 ? 0 : 4 - c;
+}
+int tile_panels(int ld, int xbytes) {
+  const int pc = kTileLanes * tile_cpl(ld, xbytes);
+  return (ld + pc - 1) / pc;
 }
 
 int spmm_tile_key(const SpmmItem& it) {
@@ -516,7 +527,7 @@ static hipError_t tile_launch(hipStream_t st, SpmmItem* items, const int* idx, i
     SpmmItem& it = items[idx[q]];
     TileDesc& d = bt.d[q];
     const RowTiles& rt = it.rg.tile;
-    d.npan = (it.g.ld + kTileLanes * CPL - 1) / (kTileLanes * CPL);
+    d.npan = tile_panels(it.g.ld, it.g.xbytes);
     // one resident wave of blocks over all panels, a multiple of 8 per panel
     // from 8 up (see chunk_of)
     int nb = (int)std::min<int64_t>(rt.shape.ntile, std::max(1, resident / d.npan));

@@ -321,6 +321,10 @@ hipError_t launch_spmm_rg_group(hipStream_t st, SpmmItem* items, const int* idx,
 // Non-zero where an item takes the row-tile product (g.rg = 2, on a matrix
 // that keeps tiles, of at least 16 columns): items of one launch share the key.
 int spmm_tile_key(const SpmmItem& it);
+// Blocks per CU of the row-tile product on unions of up to `rows` columns (0:
+// too many), and its panels of a block of ld columns.
+int tile_blocks(int rows, int ld, int xbytes);
+int tile_panels(int ld, int xbytes);
 hipError_t launch_spmm_tile_group(hipStream_t st, SpmmItem* items, const int* idx, int cnt);
 // Grid of a streaming kernel `fn` over g's rows (row groups with g.rg): at
 // most one resident wave of blocks, a multiple of 8 from 8 blocks up; even: two

@@ -479,12 +479,46 @@ static std::pair<int, int> rowgroup_default(int ld, int xbytes) {
   return {(ncolv + C - 1) / C, C};
 }
 
+// Whether the row-tile product is the faster one.  It is where a CU holds two or
+// three blocks of the largest union's LDS (estimates against the row-group
+// product, or the CSR product where that is the default: 0.55 to 1.01 of the
+// time).  At one block per CU nothing hides a
+// tile's gathers, and it stays ahead
+// - of the CSR product (FP64 values on FP32 vectors) where neighbouring tiles
+//   share columns (covariances of 150 to 420 entries per row: 0.59 to 0.87) or
+//   every gathered column serves two groups (random graphs of 8 to 32 unknowns
+//   per node 0.57 to 0.91; of 4 to 6 unknowns 1.07 to 1.20),
+// - on one panel of columns (20 and 30 FP32, 16 FP64 columns: 0.57 to 1.02);
+// on several panels, each gathered again, only where neighbouring tiles share
+// columns (on random graphs of 4 to 32 unknowns per node 1.02 to 1.32 with 64
+// and 128 FP32 or 30 and 64 FP64 columns), and there
+// - where the large unions are few (one row of 800 more columns: 0.23 to 0.63),
+// - with two panels of FP64 columns (0.74 to 0.85; of four 0.80 to 1.12),
+// but not on several FP32 panels (64 columns 1.00 to 1.05).  Of tiles that share
+// nothing, more than two panels lose at two blocks per CU (0.97 to 1.10), and
+// with any where the block is larger than the 256 MB of the last-level cache,
+// from which every panel's lines then come again (1.6e6 rows, 64 FP64 columns
+// 1.04 to 1.06, 128 FP32 1.01 to 1.02; 400 000 rows 0.96 to 1.00).
+bool Run::tiles_pay(int ld) const {
+  if (!a_->tl_col || ld < kTileMinCols) return false;
+  const int blocks = tile_blocks(a_->tl_umax, ld, xb_), panels = tile_panels(ld, xb_);
+  const bool local = a_->tl_local, over_csr = mixed_ && a_->vt_lo == VT_F64;
+  if (!local && !over_csr && panels > 2 && n_ * ld * xb_ > int64_t(256) << 20) return false;
+  if (blocks >= 3) return true;
+  if (blocks == 2 && (local || panels <= 2)) return true;
+  if (over_csr) return local || a_->rg_nu >= 2 * a_->tl_total;
+  if (panels == 1) return true;
+  if (!local) return false;
+  return tile_blocks((int)(a_->tl_total / a_->tl_shape.ntile), ld, xb_) >= 3 ||
+         (xb_ == 8 && panels == 2);
+}
+
 // Row tiles set their own lanes, so they are what the row groups' default
-// geometry stands for where the matrix keeps them; any other lanes and chunks
-// take the row-group product.
+// geometry stands for where they pay; any other lanes and chunks take the
+// row-group product.
 Geom Run::product_geom(Geom g) const {
   g.band = a_->band;
-  if (g.rg && a_->tl_col && g.ld >= kTileMinCols &&
+  if (g.rg && tiles_pay(g.ld) &&
       std::make_pair(g.L, g.C) == rowgroup_default(g.ld, g.xbytes))
     g.rg = 2;
   return g;
@@ -509,11 +543,11 @@ Geom Run::krylov_geom(int ld, int which) const {
 
 // The untuned geometry.
 Geom Run::default_geom(int ld, int which) const {
-  if (which == 0 && rg_ok() && ld >= 16 && (!(mixed_ && a_->vt_lo == VT_F64) || a_->tl_col)) {
+  if (which == 0 && rg_ok() && ld >= 16 && (!(mixed_ && a_->vt_lo == VT_F64) || tiles_pay(ld))) {
     // row groups (blocks of 16 columns or more: on narrower ones the groups'
     // extra multiply-adds and shuffles weigh more than the gathers they save).
-    // FP64 values on FP32 vectors take them only where the matrix keeps row
-    // tiles (estimates, tiles against the CSR product: scattered covariances of
+    // FP64 values on FP32 vectors take them only where their tiles pay
+    // (estimates, tiles against the CSR product: scattered covariances of
     // 3K to 200K rows, 16 to 96 probes, 0.63 to 0.99 of the time, grid ones 0.56
     // to 0.90); the row-group product's FP64 sums of 4 rows cost it occupancy
     // (22.3 against 21.3 ms), but the autotuner and ld_tune_set can still take it
@@ -2119,7 +2153,8 @@ static hipError_t drop_tiles(ld_matrix* m) {
 
 // Tiles of the matrix's row groups on the device; kept where every tile's
 // union fits the LDS of a block.
-static hipError_t build_tiles(hipStream_t st, ld_matrix* m, const TileShape& s) {
+static hipError_t build_tiles(hipStream_t st, ld_matrix* m, const int32_t* rp, const int32_t* ci) {
+  const TileShape s = choose_tile_shape(m->n, rp, ci);
   const int64_t ng = (m->n + kRowGroup - 1) / kRowGroup;
   std::vector<int32_t> cnt((size_t)s.ntile);
   hipError_t e = hipMalloc(&m->tl_cnt, (size_t)s.ntile * 4);
@@ -2130,9 +2165,11 @@ static hipError_t build_tiles(hipStream_t st, ld_matrix* m, const TileShape& s) 
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) return e;
   int ust = 0;
+  int64_t total = 0;
   for (int32_t c : cnt) {
     if (c < 1 || c > kTileMaxUnion) return hipSuccess;  // no tiles (the count buffer stays)
     ust = std::max(ust, c);
+    total += c;
   }
   const int umax = ust;
   ust = (ust + kTileLoadRows - 1) / kTileLoadRows * kTileLoadRows;
@@ -2145,6 +2182,13 @@ static hipError_t build_tiles(hipStream_t st, ld_matrix* m, const TileShape& s) 
   if (e == hipSuccess) {
     m->tl_ust = ust;
     m->tl_umax = umax;
+    m->tl_total = total;
+    // covariances and meshes in natural order share 0.1 to 0.8, random graphs
+    // up to 0.07
+    ColumnSet set(m->n);
+    double shared = 0.0;
+    sample_tiles(m->n, rp, ci, s, set, &shared);
+    m->tl_local = shared >= 0.1;
     m->tl_shape = s;
     m->bytes += (size_t)s.ntile * (4 + (size_t)ust * 4) + ((size_t)m->rg_nu + (size_t)ng) * 2;
   }
@@ -2361,7 +2405,7 @@ ld_status ld_create_csr(ld_ctx* ctx, int64_t n, int64_t nnz, const int32_t* row_
         if (e == hipSuccess) {
           m->rg_nu = nu;
           m->bytes += ((size_t)ng + 1) * 4 + (size_t)nu * (4 + (f32 ? 12 : 8) * kRowGroup);
-          e = build_tiles(ctx->stream, m.get(), choose_tile_shape(n, row_ptr, col_idx));
+          e = build_tiles(ctx->stream, m.get(), row_ptr, col_idx);
         }
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
       } else if (e == hipSuccess) {

@@ -171,6 +171,8 @@ struct ld_matrix {
   int* tl_cnt = nullptr;
   uint16_t* tl_idx = nullptr;   // one per group entry, then one per group
   int tl_ust = 0, tl_umax = 0;
+  int64_t tl_total = 0;   // columns of all tiles' unions together
+  bool tl_local = false;  // neighbouring tiles share columns (Run::tiles_pay)
   ld::TileShape tl_shape;
   int band = 0;  // frequent stride of the CSR rows from kBandStride on, 0 = none (Geom::band)
   double lo_hint = 0, hi_hint = 0;
@@ -245,6 +247,7 @@ class Run {
   // a product geometry as it runs on this matrix: its frequent stride, and row
   // tiles for row groups in their default geometry
   Geom product_geom(Geom g) const;
+  bool tiles_pay(int ld) const;   // the row groups' default is their tiles
   bool rg_ok() const;             // the product may read the matrix's row groups
   RowGroups row_groups() const;
   int upd_steady_nv(bool presub) const;  // update vectors of a steady-state step

@@ -19,7 +19,13 @@ class ColumnSet {
     w |= m;
     return !(old & m);
   }
-  void remove(int32_t c) { bits_[(size_t)c >> 6] &= ~(uint64_t(1) << (c & 63)); }
+  // true where c was in it
+  bool remove(int32_t c) {
+    uint64_t& w = bits_[(size_t)c >> 6];
+    const uint64_t m = uint64_t(1) << (c & 63), old = w;
+    w &= ~m;
+    return (old & m) != 0;
+  }
 
  private:
   std::vector<uint64_t> bits_;
@@ -38,17 +44,21 @@ inline void for_tile_columns(int64_t n, const int32_t* rp, const int32_t* ci, co
   }
 }
 
-// Distinct columns of 8 sampled tiles of the given shape, per tile.  `set` is
-// empty before and after.
+// Distinct columns of 8 sampled tiles of the given shape, per tile, and the part
+// of them that the next tile has too (`shared`, may be null).  `set` is empty
+// before and after.
 inline double sample_tiles(int64_t n, const int32_t* rp, const int32_t* ci, const TileShape& s,
-                           ColumnSet& set) {
+                           ColumnSet& set, double* shared = nullptr) {
   const int ns = (int)std::min<int64_t>(s.ntile, 8);
-  int64_t total = 0;
+  int64_t total = 0, common = 0;
   for (int i = 0; i < ns; ++i) {
     const int64_t tile = (2 * i + 1) * s.ntile / (2 * ns);
     for_tile_columns(n, rp, ci, s, tile, [&](int32_t c) { total += set.add(c); });
+    if (shared && tile + 1 < s.ntile)
+      for_tile_columns(n, rp, ci, s, tile + 1, [&](int32_t c) { common += set.remove(c); });
     for_tile_columns(n, rp, ci, s, tile, [&](int32_t c) { set.remove(c); });
   }
+  if (shared) *shared = total > 0 ? (double)common / (double)total : 0.0;
   return ns > 0 ? (double)total / ns : 0.0;
 }
 

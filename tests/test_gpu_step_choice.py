@@ -171,3 +171,46 @@ def test_tuner_times_the_default(L, ctx, npr, prec, vt):
         assert L.ld_debug_step_paths(h, p) == tuned
     finally:
         ctx.release(h)
+
+
+def _dofs(graph, b):
+    """b unknowns per node of a graph Laplacian: dense b x b blocks."""
+    return _csr(sp.kron(graph.to_scipy(), np.eye(b) * 2 + 0.5, format="csr"))
+
+
+# the row groups' default is their tiles where these pay.  Random graphs: at one
+# block of the largest union's LDS per CU one panel of columns alone, at two
+# blocks two panels; a covariance of 190 entries per row (one block per CU): FP64
+# up to two panels, FP32 one; with a few large unions all
+@pytest.mark.parametrize("name,npr,prec,vt,product", [
+    ("random_1", 16, "mixed", "fp32", 2), ("random_1", 32, "mixed", "fp32", 2),
+    ("random_1", 33, "mixed", "fp32", 1), ("random_1", 16, "fp64", "fp64", 2),
+    ("random_1", 17, "fp64", "fp64", 1), ("random_1", 30, "mixed", "fp64", 0),
+    ("random_2", 64, "mixed", "fp32", 2), ("random_2", 65, "mixed", "fp32", 2),
+    ("random_25", 64, "mixed", "fp32", 2), ("random_25", 65, "mixed", "fp32", 1),
+    ("random_3", 65, "mixed", "fp32", 2), ("random_16", 30, "mixed", "fp64", 2),
+    ("random_big", 64, "fp64", "fp64", 1), ("random_big", 32, "fp64", "fp64", 2),
+    ("wide", 33, "mixed", "fp32", 1), ("wide", 32, "mixed", "fp32", 2),
+    ("wide", 32, "fp64", "fp64", 2), ("wide", 33, "fp64", "fp64", 1),
+    ("wide", 64, "mixed", "fp64", 2), ("hub", 64, "mixed", "fp32", 2),
+    ("hub", 64, "fp64", "fp64", 2),
+])
+def test_tiles_where_they_pay(L, ctx, name, npr, prec, vt, product):
+    def hub():
+        a = W.wendland(20000, 48.0, NUG, seed=1).to_scipy().tolil()
+        cols = np.arange(0, 20000, 25)
+        a[7000, cols] = a[7000, cols].toarray() + 1e-4
+        a[cols, 7000] = a[cols, 7000].toarray() + 1e-4
+        return _csr(a)
+    a = {"random_1": lambda: _dofs(W.er_laplacian(6000, 6000 * 5, seed=1), 4),
+         "random_2": lambda: _dofs(W.er_laplacian(6000, 6000 * 2, seed=1), 4),
+         "random_25": lambda: _dofs(W.er_laplacian(6000, 6000 * 5 // 2, seed=1), 4),
+         "random_3": lambda: _dofs(W.er_laplacian(6000, 6000 * 1, seed=1), 4),
+         "random_16": lambda: _dofs(W.er_laplacian(2000, 2000 * 3, seed=1), 16),
+         "random_big": lambda: _dofs(W.er_laplacian(140000, 140000, seed=1), 4),
+         "wide": lambda: W.wendland_grid(100, 120, 8.0, nugget=NUG), "hub": hub}[name]()
+    got = _paths(L, ctx, a, npr, prec, vt, lo=1e-2)
+    print(f"  {got}", flush=True)
+    blocks = {"random_1": 1, "random_16": 1, "random_25": 2, "wide": 1, "hub": 1}.get(name, 3)
+    rows = {1: (633, 1248), 2: (413, 632), 3: (1, 412)}[blocks]  # of 128 bytes in 52.5 and 80 KB
+    assert rows[0] <= got["tile_union"] <= rows[1] and got["product"] == product
