@@ -1434,9 +1434,15 @@ static bool spmm_few(const SpmmItem& it) {
 // the rounds of chunk_of: 48^3 to 160^3 rows, 30 to 128 probes, FP64 and FP32
 // vectors 0.93 to 1.00 of the time (61^3 rows with 96 FP32 probes 3.00 against
 // 3.11 ms; 128^3 with 64 is the one at 1.007); 2-D grids of lines from 2048
-// rows 0.97 to 1.00, of 300 to 1500 rows 0.98 to 1.04, hence kBandStride.
+// rows 0.97 to 1.00, of 300 to 1500 rows 0.98 to 1.04, hence kBandStride.  A
+// partial last run goes to its first bands' XCDs alone, so the rows have to be
+// whole runs but for 2% of them, as a grid's are (strides of 2100 to 300 000
+// rows, 2 to 20 whole runs 0.94 to 1.02 of the time; 1.35 runs 1.00 to 1.16, 2.1
+// runs 1.03 to 1.13, 4.3 runs 0.97 to 1.07, 8.2 runs 0.97 to 1.03).
 static BandMap spmm_bands(const Geom& g, int nblk) {
   if (g.band <= 0 || g.xil || g.ts || g.lges || g.rg || nblk % 8 != 0) return BandMap{};
+  const int64_t part = g.n % g.band;
+  if (part != 0 && 50 * (g.band - part) > g.n) return BandMap{};
   const BandMap b = make_band_map(g.band, rows_per_block(g.L));
   return (b.m >> kBandShift) >= 8 ? b : BandMap{};
 }

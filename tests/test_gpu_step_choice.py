@@ -214,3 +214,19 @@ def test_tiles_where_they_pay(L, ctx, name, npr, prec, vt, product):
     blocks = {"random_1": 1, "random_16": 1, "random_25": 2, "wide": 1, "hub": 1}.get(name, 3)
     rows = {1: (633, 1248), 2: (413, 632), 3: (1, 412)}[blocks]  # of 128 bytes in 52.5 and 80 KB
     assert rows[0] <= got["tile_union"] <= rows[1] and got["product"] == product
+
+
+# bands: strides from 2048 rows and 8 chunks of rows per band on, whole runs of the
+# stride but for 2% of the rows (60 runs less 40 or 1200 rows, 2.1 runs), and more
+# rows than the latency instance takes
+@pytest.mark.parametrize("n,strides,npr,prec,bands", [
+    (100 * 2048, (1, 32, 2048), 96, "mixed", 1), (100 * 2047, (1, 32, 2047), 96, "mixed", 0),
+    (60 * 2500 - 40, (1, 50, 2500), 96, "mixed", 1), (60 * 2500 - 1200, (1, 50, 2500), 96, "mixed", 1),
+    (10 * 15000 - 1200, (1, 50, 15000), 96, "mixed", 1),
+    (10 * 15000 - 4000, (1, 50, 15000), 96, "mixed", 0),
+    (21 * 7000, (1, 50, 70000), 96, "mixed", 0), (2 * 70000, (1, 50, 70000), 96, "mixed", 1),
+    (20 * 2048, (1, 32, 2048), 30, "mixed", 0), (120 * 4096, (1, 50, 4096), 8, "fp64", 1),
+    (120 * 4095, (1, 50, 4095), 8, "fp64", 0), (60 * 2048, (1, 50, 2048), 5, "half", 0),
+])
+def test_bands_of_whole_runs(L, ctx, n, strides, npr, prec, bands):
+    assert _paths(L, ctx, _stripes(n, strides), npr, prec)["bands"] == bands
