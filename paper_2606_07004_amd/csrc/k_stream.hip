@@ -1438,11 +1438,17 @@ static bool spmm_few(const SpmmItem& it) {
 // partial last run goes to its first bands' XCDs alone, so the rows have to be
 // whole runs but for 2% of them, as a grid's are (strides of 2100 to 300 000
 // rows, 2 to 20 whole runs 0.94 to 1.02 of the time; 1.35 runs 1.00 to 1.16, 2.1
-// runs 1.03 to 1.13, 4.3 runs 0.97 to 1.07, 8.2 runs 0.97 to 1.03).
+// runs 1.03 to 1.13, 4.3 runs 0.97 to 1.07, 8.2 runs 0.97 to 1.03).  Runs of a
+// multiple of 4 MB, the size of an XCD's L2: rows a stride apart meet in the same
+// sets, and on rows of up to 256 bytes the plain order is faster (16 384 and
+// 32 768 rows of 256 bytes 1.01 to 1.03, 16 000 and 16 584 rows 0.98 to 0.99; of
+// 512 bytes 0.95 to 1.01).
 static BandMap spmm_bands(const Geom& g, int nblk) {
   if (g.band <= 0 || g.xil || g.ts || g.lges || g.rg || nblk % 8 != 0) return BandMap{};
   const int64_t part = g.n % g.band;
   if (part != 0 && 50 * (g.band - part) > g.n) return BandMap{};
+  const int64_t row = (int64_t)g.ld * g.xbytes;
+  if (row <= 256 && g.band * row % (int64_t(4) << 20) == 0) return BandMap{};
   const BandMap b = make_band_map(g.band, rows_per_block(g.L));
   return (b.m >> kBandShift) >= 8 ? b : BandMap{};
 }

@@ -217,8 +217,9 @@ def test_tiles_where_they_pay(L, ctx, name, npr, prec, vt, product):
 
 
 # bands: strides from 2048 rows and 8 chunks of rows per band on, whole runs of the
-# stride but for 2% of the rows (60 runs less 40 or 1200 rows, 2.1 runs), and more
-# rows than the latency instance takes
+# stride but for 2% of the rows (60 runs less 40 or 1200 rows, 2.1 runs), more rows
+# than the latency instance takes, and not where rows of up to 256 bytes make a run
+# a multiple of 4 MB
 @pytest.mark.parametrize("n,strides,npr,prec,bands", [
     (100 * 2048, (1, 32, 2048), 96, "mixed", 1), (100 * 2047, (1, 32, 2047), 96, "mixed", 0),
     (60 * 2500 - 40, (1, 50, 2500), 96, "mixed", 1), (60 * 2500 - 1200, (1, 50, 2500), 96, "mixed", 1),
@@ -227,6 +228,9 @@ def test_tiles_where_they_pay(L, ctx, name, npr, prec, vt, product):
     (21 * 7000, (1, 50, 70000), 96, "mixed", 0), (2 * 70000, (1, 50, 70000), 96, "mixed", 1),
     (20 * 2048, (1, 32, 2048), 30, "mixed", 0), (120 * 4096, (1, 50, 4096), 8, "fp64", 1),
     (120 * 4095, (1, 50, 4095), 8, "fp64", 0), (60 * 2048, (1, 50, 2048), 5, "half", 0),
+    (16 * 16384, (1, 128, 16384), 64, "mixed", 0), (16 * 16384, (1, 128, 16384), 60, "mixed", 1),
+    (16 * 16384, (1, 128, 16384), 68, "mixed", 1), (16 * 16384, (1, 128, 16384), 128, "mixed", 1),
+    (16 * 16384, (1, 128, 16384), 30, "fp64", 0), (16 * 16400, (1, 128, 16400), 64, "mixed", 1),
 ])
 def test_bands_of_whole_runs(L, ctx, n, strides, npr, prec, bands):
     assert _paths(L, ctx, _stripes(n, strides), npr, prec)["bands"] == bands
