@@ -235,7 +235,9 @@ ld_status ld_destroy(ld_matrix* a);
 ld_status ld_matrix_bounds(const ld_matrix* a, double* lambda_lo, double* lambda_hi);
 /* x^T Q x for a host vector x[n] (caller-owned), on the device in FP64: the
  * data term of the Gaussian log-likelihood of Section 4,
- * L(theta) = log det Q / 2 - x^T Q x / 2 - n log(2 pi) / 2.  Blocking. */
+ * L(theta) = log det Q / 2 - x^T Q x / 2 - n log(2 pi) / 2.  Blocking.  Its
+ * device buffer (8 bytes per row of the largest such matrix and 16 KB) stays
+ * with the context until the last of its matrices is destroyed. */
 ld_status ld_quad_form(ld_matrix* a, const double* x, double* out);
 
 /* Blocking estimate with the context's default method and precision and

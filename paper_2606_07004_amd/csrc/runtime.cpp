@@ -2083,6 +2083,7 @@ ld_status ld_ctx_destroy(ld_ctx* ctx) {
   if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
   ctx->graphs.clear();
   ctx->workspace.release();
+  ctx->quad.release();
   if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
   for (hipEvent_t& e : ctx->na_ev)
     if (e) (void)hipEventDestroy(e);
@@ -2474,7 +2475,10 @@ ld_status ld_destroy(ld_matrix* a) {
   if (a->tl_col) (void)hipFree(a->tl_col);
   if (a->tl_cnt) (void)hipFree(a->tl_cnt);
   if (a->tl_idx) (void)hipFree(a->tl_idx);
-  a->ctx->n_matrices.fetch_sub(1);
+  {
+    std::lock_guard<std::mutex> lk(a->ctx->est_mu);
+    if (a->ctx->n_matrices.fetch_sub(1) == 1) a->ctx->quad.release();
+  }
   delete a;
   return LD_OK;
 }
@@ -2528,13 +2532,15 @@ ld_status ld_quad_form(ld_matrix* a, const double* x, double* out) {
   ld_ctx* ctx = a->ctx;
   std::lock_guard<std::mutex> lk(ctx->est_mu);
   LD_HIP_API(hipSetDevice(ctx->device));
-  // x, the blocks' sums and the result in the context's workspace (kept
-  // between calls; the estimates' buffers, which the calls of a context use
-  // one at a time)
+  // x, the blocks' sums and the result in a buffer of their own, kept between
+  // calls while the context has matrices (the estimates' workspace holds the
+  // captured graphs' buffers: growing it here would drop them)
   const size_t vec = align_up((size_t)a->n * 8), part = (size_t)kMaxBlocks * 8;
-  const ld_status rc = ensure_workspace(ctx, vec + part + 64);
-  if (rc != LD_OK) return rc;
-  char* base = static_cast<char*>(ctx->workspace.ptr);
+  const hipError_t e = ctx->quad.ensure(vec + part + 64);
+  if (e != hipSuccess)
+    return set_error(e == hipErrorOutOfMemory ? LD_E_NO_MEMORY : LD_E_DEVICE,
+                     std::string("quadratic form: ") + hipGetErrorString(e));
+  char* base = static_cast<char*>(ctx->quad.ptr);
   double* X = reinterpret_cast<double*>(base);
   double* pt = reinterpret_cast<double*>(base + vec);
   double* res = reinterpret_cast<double*>(base + vec + part);

@@ -128,6 +128,7 @@ struct ld_ctx {
   ld_ctx_opts opts{};
   std::mutex est_mu;             // blocking estimates share the stream and workspace
   ld::DeviceBuffer workspace;
+  ld::DeviceBuffer quad;         // ld_quad_form, while the context has matrices
   std::atomic<int> n_matrices{0};
   std::unique_ptr<ld::Server> server;
   std::mutex server_mu;

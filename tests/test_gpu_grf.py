@@ -105,3 +105,28 @@ def test_quad_form_shapes(L, name):
     # about 100 roundings (2^-53 each) of partial sums bounded by sum |x_i a_ij x_j|
     bound = float(np.abs(x) @ (abs(a.to_scipy()) @ np.abs(x)))
     assert abs(got - want) <= 1e-13 * bound
+
+
+def test_quad_form_keeps_captured_estimates(L):
+    # a quadratic form larger than the estimates' workspace leaves the captured
+    # graphs alone: the next estimate of the small matrix is a replay
+    print("\n[case] quad form beside a captured estimate", flush=True)
+    small, large = W.lap2d(24, 0.1), W.diag_matrix(np.full(3_000_000, 2.0))
+    with L.Context(0) as c:
+        hs, hl = c.matrix(small), c.matrix(large)
+        p = L.make_params(8, 2, 10, 2, 7)
+        assert L.ld_request_bytes(hs, p) < 8 * large.n
+        first = [L.ld_estimate_ex(hs, p).logdet for _ in range(3)]
+        before = L.ld_graph_stats_get(c.handle)
+        assert before.replays >= 1 and before.cached == 1
+        assert L.ld_quad_form(hl, np.ones(large.n)) == 2.0 * large.n
+        again = L.ld_estimate_ex(hs, p).logdet
+        after = L.ld_graph_stats_get(c.handle)
+        assert (after.captures, after.cached) == (before.captures, 1)
+        assert after.replays == before.replays + 1
+        assert first == [again] * 3
+        # the form's buffer goes with the last matrix and comes back
+        c.release(hs)
+        c.release(hl)
+        hl = c.matrix(large)
+        assert L.ld_quad_form(hl, np.ones(large.n)) == 2.0 * large.n
