@@ -218,9 +218,10 @@ const char* ld_last_error(void);
  * ld_autotune): per union column its index and 4 FP64 values (plus 4 FP32
  * ones with LD_VT_FP32), 36 or 52 bytes, built on the device here when
  * groups of 4 rows hold at least 2 entries per union column (so at most
- * 18 or 26 bytes per entry), and tiles of 16 groups (2 bytes per union
- * column, 4 per column of a tile's union and 2 per row group: 2 bytes per
- * entry or less).
+ * 18 or 26 bytes per entry), and, where no 64 rows of a tile reference more
+ * than 1248 columns, tiles of 16 groups: 2 bytes per union column and per
+ * group, and for every tile 4 bytes and 4 per column of the widest tile's
+ * union rounded up to 64 (5 KB per tile at most, 80 bytes per row).
  * lambda_lo_hint / lambda_hi_hint > 0 replace the Gershgorin bounds
  * (Section 2.1); a Gershgorin lower bound <= 0 without a hint is replaced by
  * 1e-6 * lambda_hi.  n and nnz must fit int32. */

@@ -60,13 +60,7 @@ Geom make_geom(int64_t n, int ld, int xbytes);
 Geom make_geom_lc(int64_t n, int ld, int xbytes, int L, int C);
 bool geom_usable(const Geom& g);
 
-// Row groups of a CSR matrix: rows kRowGroup g .. kRowGroup g + kRowGroup - 1
-// form group g; its entries are the sorted union of the rows' columns,
-// col[gp[g] .. gp[g+1]), and for each union column u the kRowGroup values
-// val[kRowGroup u + r] of row r (zero where the row has no entry there).
-// One gather of a neighbour's probe row then serves every row of the group
-// that references it; the rows' sums see their nonzero terms in CSR order.
-
+// Tiles of kTileGroups row groups (row_tiles.h, k_rowtile.hip).
 struct RowTiles {
   const int* tcol = nullptr;       // [ntile][ust] sorted union columns of each tile (the last repeated)
   const int* tcnt = nullptr;       // [ntile] their number
@@ -75,6 +69,12 @@ struct RowTiles {
   int ust = 0, umax = 0;           // umax: the largest tcnt; ust a multiple of kTileLoadRows
   TileShape shape;
 };
+// Row groups of a CSR matrix: rows kRowGroup g .. kRowGroup g + kRowGroup - 1
+// form group g; its entries are the sorted union of the rows' columns,
+// col[gp[g] .. gp[g+1]), and for each union column u the kRowGroup values
+// val[kRowGroup u + r] of row r (zero where the row has no entry there).
+// One gather of a neighbour's probe row then serves every row of the group
+// that references it; the rows' sums see their nonzero terms in CSR order.
 struct RowGroups {
   const int* gp = nullptr;
   const int* col = nullptr;

@@ -2168,7 +2168,10 @@ static hipError_t build_tiles(hipStream_t st, ld_matrix* m, const int32_t* rp, c
   int ust = 0;
   int64_t total = 0;
   for (int32_t c : cnt) {
-    if (c < 1 || c > kTileMaxUnion) return hipSuccess;  // no tiles (the count buffer stays)
+    if (c < 1 || c > kTileMaxUnion) {  // no tiles (the count buffer stays)
+      m->bytes += (size_t)s.ntile * 4;
+      return hipSuccess;
+    }
     ust = std::max(ust, c);
     total += c;
   }
@@ -2191,7 +2194,8 @@ static hipError_t build_tiles(hipStream_t st, ld_matrix* m, const int32_t* rp, c
     sample_tiles(m->n, rp, ci, s, set, &shared);
     m->tl_local = shared >= 0.1;
     m->tl_shape = s;
-    m->bytes += (size_t)s.ntile * (4 + (size_t)ust * 4) + ((size_t)m->rg_nu + (size_t)ng) * 2;
+    m->bytes += (size_t)s.ntile * (4 + (size_t)ust * 4) +
+                ((size_t)m->rg_nu + kTilePad + (size_t)ng) * 2;
   }
   return e;
 }
@@ -2405,7 +2409,8 @@ ld_status ld_create_csr(ld_ctx* ctx, int64_t n, int64_t nnz, const int32_t* row_
                                    m->rg_val, m->rg_val64);
         if (e == hipSuccess) {
           m->rg_nu = nu;
-          m->bytes += ((size_t)ng + 1) * 4 + (size_t)nu * (4 + (f32 ? 12 : 8) * kRowGroup);
+          m->bytes += ((size_t)ng + 1) * 4 + (size_t)nu * 4 +
+                      ((size_t)nu + kTilePad) * (f32 ? 12 : 8) * kRowGroup;
           e = build_tiles(ctx->stream, m.get(), row_ptr, col_idx);
         }
         if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
