@@ -266,27 +266,27 @@ __device__ inline void spmm_body(int64_t n, int Lr, int lgES_arg, const int* __r
           if (FUSED && c0 == row) xd[c] = x;
         }
     };
-    // entry positions less kRound, the most a round takes: the round past a row
-    // that ends at 2^31 - 1, the largest entry count of a matrix, would start
-    // beyond an int (unsigned positions cost two registers, a wave per SIMD in
-    // some instances)
-    constexpr int kRound = 64 * KE;
-    const int kbeg = rp[row] - kRound;
-    const int kend = rp[row + 1] - kRound;
+    // positions are compared as unsigned: the round past a row that ends at
+    // 2^31 - 1, the largest entry count of a matrix, starts beyond an int.  The
+    // loads index with ints (with unsigned or shifted positions they cost two
+    // registers, or 73 -> 76 us on 660^2 rows with 27 FP64 probes)
+    const int kbeg = rp[row];
+    const int kend = rp[row + 1];
     // the row's L lanes load KE * L consecutive entries (column, value) per
     // round, lane l holding entries l, l + L, ..., and pass them around the
     // group by lane shuffles; entries are accumulated in order
-    for (int base = kbeg; base < kend; base += rm.L * KE) {
+    for (int base = kbeg; (unsigned)base < (unsigned)kend;
+         base = (int)((unsigned)base + (unsigned)(rm.L * KE))) {
       int myc[KE];
       A mya[KE];
 #pragma unroll
       for (int u = 0; u < KE; ++u) {
-        const int kk = base + rm.gl + rm.L * u;
+        const int kk = (int)((unsigned)base + (unsigned)(rm.gl + rm.L * u));
         myc[u] = row;
         mya[u] = A(0);
-        if (kk < kend) {
-          myc[u] = ci[(int64_t)kk + kRound];
-          mya[u] = value_as<VT, A>(va[(int64_t)kk + kRound]);
+        if ((unsigned)kk < (unsigned)kend) {
+          myc[u] = ci[kk];
+          mya[u] = value_as<VT, A>(va[kk]);
         }
       }
 #pragma unroll
