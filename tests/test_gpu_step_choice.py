@@ -234,3 +234,38 @@ def test_tiles_where_they_pay(L, ctx, name, npr, prec, vt, product):
 ])
 def test_bands_of_whole_runs(L, ctx, n, strides, npr, prec, bands):
     assert _paths(L, ctx, _stripes(n, strides), npr, prec)["bands"] == bands
+
+
+# values at the sizes where the rules above change, against the step with two
+# chunks per lane (another product and another update): each row's sums are the
+# same chains of multiply-adds, the FP64 sums of inner products differ by their
+# order (1e-10), FP32 and FP16 vectors by single roundings of 2^-24 and 2^-11
+# after them (1e-6, 5e-4)
+@pytest.mark.parametrize("n,npr,prec,vt,k", [
+    (16 * 24 * 2048 + 1, 64, "mixed", "fp32", 2), (16 * 24 * 2048, 64, "mixed", "fp32", 3),
+    (16 * 12 * 2048 + 1, 30, "fp64", "fp64", 4), (256 * 320 + 1, 4, "mixed", "fp32", 2),
+    (128 * 320 + 1, 4, "fp64", "fp64", 3), (64 * 320 + 1, 30, "half", "fp32", 2),
+    (64 * 1024 + 1, 30, "half", "fp32", 2), (16 * 3072 + 1, 30, "fp64", "fp64", 10),
+    (16 * 3072, 30, "fp64", "fp64", 10), (32 * 3072, 30, "mixed", "fp64", 2),
+    (20011, 8, "mixed", "fp64", 2), (20011, 60, "half", "fp32", 2),
+])
+def test_values_where_rules_change(L, ctx, n, npr, prec, vt, k):
+    a = _stripes(n, (1, 37))
+    a.values[a.col_idx == np.repeat(np.arange(n), np.diff(a.row_ptr))] += \
+        np.random.default_rng(n).uniform(0, 1, n)
+    vec = {"fp64": 2, "mixed": 4, "half": 8}[prec]
+    nc = -(-npr // vec) if prec == "half" else -(-npr // 4) * (4 // vec)
+    h = ctx.matrix(a, vt=L.LD_VT_FP64 if vt == "fp64" else L.LD_VT_FP32)
+    try:
+        p = L.make_params(npr, max(1, npr // 3), 12, k, 3, precision={
+            "fp64": L.LD_PREC_FP64, "mixed": L.LD_PREC_MIXED, "half": L.LD_PREC_HALF}[prec])
+        print(f"\n[case] values n={n} probes {npr} {prec} values {vt} window {k} "
+              f"{L.ld_debug_step_paths(h, p)}", flush=True)
+        got = L.ld_estimate_detail(h, p)[1]["probe_K"]
+        L.ld_tune_set(h, p, -(-nc // 2), 2, -(-nc // 2), 2)
+        ref = L.ld_estimate_detail(h, p)[1]["probe_K"]
+    finally:
+        ctx.release(h)
+    assert np.all(np.isfinite(ref)) and np.all(ref != 0)
+    tol = {"fp64": 1e-10, "mixed": 1e-6, "half": 5e-4}[prec]
+    assert np.max(np.abs(got - ref) / np.abs(ref)) <= tol
