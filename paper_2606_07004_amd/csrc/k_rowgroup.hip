@@ -12,10 +12,11 @@
 // ratio of entries to union columns.  A row's sum sees its own nonzero terms
 // in CSR order (a zero value adds an exact zero), so W is the CSR product's
 // W; the epilogue (scaling, early subtraction, store, fused inner products)
-// is the CSR product's, per row.  Blocks of 16 columns or more on matrices
-// whose tiles of 16 groups fit a block's LDS take the row-tile product
-// (k_rowtile.hip) instead: this one serves narrower blocks (its gathers are
-// short there and a 128-byte panel would idle) and matrices of very long rows.
+// is the CSR product's, per row.  Blocks of 16 columns or more take the
+// row-tile product (k_rowtile.hip) instead by default where the matrix's tiles
+// pay (Run::tiles_pay): this one serves narrower blocks (its gathers are short
+// there and a 128-byte panel would idle), the other matrices and any geometry
+// that is chosen for it.
 #include <climits>
 #include <type_traits>
 

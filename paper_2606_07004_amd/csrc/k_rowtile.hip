@@ -25,8 +25,9 @@
 // 1.08e6, 30 FP32 probes) 355 -> 243, 23 000 scattered points with 30 FP64
 // probes 69 -> 21.  What bounds it now is vector issue: 76e6 wave instructions
 // on the first, 65% of them the multiply-adds (41% of those on the zeros of
-// rows that lack a column), 0.7 of the cycles, at 3 blocks of 4 waves per CU
-// (LDS).  Tried and not kept: 64 FP32 columns per panel (two blocks per CU: 294
+// rows that lack a column), 0.7 of the cycles at 4.6 clocks each, at 3 blocks of
+// 4 waves per CU (LDS); on the last, with one tile per block, the chain of
+// latencies (0.2 of the cycles issue vector instructions).  Tried and not kept: 64 FP32 columns per panel (two blocks per CU: 294
 // against 215 us), one round of entries in flight ahead (274: a round of
 // memory latency each 16 entries).
 //
