@@ -27,9 +27,10 @@
 // on the first, 65% of them the multiply-adds (41% of those on the zeros of
 // rows that lack a column), 0.7 of the cycles at 4.6 clocks each, at 3 blocks of
 // 4 waves per CU (LDS); on the last, with one tile per block, the chain of
-// latencies (0.2 of the cycles issue vector instructions).  Tried and not kept: 64 FP32 columns per panel (two blocks per CU: 294
-// against 215 us), one round of entries in flight ahead (274: a round of
-// memory latency each 16 entries).
+// latencies (vector instructions in a quarter of the cycles).  Tried and not
+// kept: 64 FP32 columns per panel (two blocks per CU: 294 against 215 us), one
+// round of entries in flight ahead (274: a round of memory latency each 16
+// entries).
 //
 // A row's sum sees its nonzero terms in CSR order (a zero value adds an exact
 // zero): W is the CSR product's W.  Only the grouping of the FP64 partial sums
