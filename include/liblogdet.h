@@ -314,10 +314,10 @@ ld_status ld_request_bytes(ld_matrix* a, const ld_params* p, uint64_t* bytes);
  * chunks per lane.  In that default geometry (as many lanes as chunks of 16
  * bytes, FP64 half as many with two chunks each) blocks of 16 columns or more
  * take the row groups in tiles of 16 whose probe rows are gathered once into
- * LDS, where every tile's union of columns fits and the tiles' unions let
- * two blocks or more share a CU or neighbouring tiles share columns; the
- * tiles set their own lanes, and any other geometry takes the row-group
- * product.  ld_autotune tries both, in both chunk mappings.  A row's sum sees its
+ * LDS, where every tile's union of columns fits and a rule on the tiles, the
+ * rows and the block's width finds them faster; the tiles set their own
+ * lanes, and any other geometry takes the row-group product.  ld_autotune
+ * tries both, in both chunk mappings.  A row's sum sees its
  * nonzero terms in CSR order, so the product's output is the CSR product's.
  * The groups are built on the device when the matrix is created.
  * ld_autotune times every such (L, C, E) with L a power of two and at most

@@ -479,38 +479,42 @@ static std::pair<int, int> rowgroup_default(int ld, int xbytes) {
   return {(ncolv + C - 1) / C, C};
 }
 
-// Whether the row-tile product is the faster one.  It is where a CU holds two or
-// three blocks of the largest union's LDS (estimates against the row-group
-// product, or the CSR product where that is the default: 0.55 to 1.01 of the
-// time).  At one block per CU nothing hides a
-// tile's gathers, and it stays ahead
-// - of the CSR product (FP64 values on FP32 vectors) where neighbouring tiles
-//   share columns (covariances of 150 to 420 entries per row: 0.59 to 0.87) or
-//   every gathered column serves two groups (random graphs of 8 to 32 unknowns
-//   per node 0.57 to 0.91; of 4 to 6 unknowns 1.07 to 1.20),
-// - on one panel of columns (20 and 30 FP32, 16 FP64 columns: 0.57 to 1.02);
-// on several panels, each gathered again, only where neighbouring tiles share
-// columns (on random graphs of 4 to 32 unknowns per node 1.02 to 1.32 with 64
-// and 128 FP32 or 30 and 64 FP64 columns), and there
-// - where the large unions are few (one row of 800 more columns: 0.23 to 0.63),
-// - with two panels of FP64 columns (0.74 to 0.85; of four 0.80 to 1.12),
-// but not on several FP32 panels (64 columns 1.00 to 1.05).  Of tiles that share
-// nothing, more than two panels lose at two blocks per CU (0.97 to 1.10), and
-// with any where the block is larger than the 256 MB of the last-level cache,
-// from which every panel's lines then come again (1.6e6 rows, 64 FP64 columns
-// 1.04 to 1.06, 128 FP32 1.01 to 1.02; 400 000 rows 0.96 to 1.00).
+// Whether the row-tile product is the faster one: estimates against the
+// row-group product, or the CSR product where that is the default (FP64 values
+// on FP32 vectors).  Three or more blocks of the largest union's LDS on a CU:
+// 0.21 to 1.01 of the time, but where the tiles share nothing and the block is
+// larger than the 256 MB of the last-level cache, from which each of more than
+// two panels' lines come again (random graphs of 1.6e6 rows, 64 FP64 columns
+// 1.04 to 1.06, 128 FP32 1.01 to 1.02).  With fewer blocks nothing hides a tile's
+// gathers, and it is a question of the rounds of blocks that the tiles and panels
+// make, since few rows leave the other products' waves idle.  Two blocks: 0.4 to
+// 1.00; tiles that share nothing and more than two panels up to 1.10 at 50 rounds
+// and more.  One block:
+// - FP64 values on FP32 vectors: where neighbouring tiles share columns 0.58 to
+//   1.00, or every gathered column serves two groups (random graphs of 8 to 32
+//   unknowns per node) 0.57 to 0.91, or up to 10 rounds 0.42 to 0.98; else (4 to 6
+//   unknowns) 0.94 to 1.20
+// - one panel of columns (up to 32 FP32 or 16 FP64): 0.25 to 1.02
+// - few large unions among small ones (a row of 800 more columns): 0.23 to 0.63
+// - FP64 up to 13.5 rounds 0.29 to 1.01, beyond them 0.80 to 1.25, or 0.80 to 0.99
+//   in one panel and a half
+// - FP32 up to 7 rounds 0.39 to 0.97, beyond them 1.00 to 1.35 in two panels; in
+//   three and more, where tiles share columns, 0.83 to 0.94 up to 16 rounds and
+//   0.92 to 1.16 beyond.
 bool Run::tiles_pay(int ld) const {
   if (!a_->tl_col || ld < kTileMinCols) return false;
+  constexpr int64_t kCus = 256;
   const int blocks = tile_blocks(a_->tl_umax, ld, xb_), panels = tile_panels(ld, xb_);
   const bool local = a_->tl_local, over_csr = mixed_ && a_->vt_lo == VT_F64;
   if (!local && !over_csr && panels > 2 && n_ * ld * xb_ > int64_t(256) << 20) return false;
   if (blocks >= 3) return true;
-  if (blocks == 2 && (local || panels <= 2)) return true;
-  if (over_csr) return local || a_->rg_nu >= 2 * a_->tl_total;
+  const int64_t work = a_->tl_shape.ntile * panels;  // blocks' tiles
+  if (blocks == 2 && (local || panels <= 2 || work <= 16 * 2 * kCus)) return true;
+  if (over_csr) return local || a_->rg_nu >= 2 * a_->tl_total || work <= 10 * kCus;
   if (panels == 1) return true;
-  if (!local) return false;
-  return tile_blocks((int)(a_->tl_total / a_->tl_shape.ntile), ld, xb_) >= 3 ||
-         (xb_ == 8 && panels == 2);
+  if (local && tile_blocks((int)(a_->tl_total / a_->tl_shape.ntile), ld, xb_) >= 3) return true;
+  if (xb_ == 8) return work <= 27 * kCus / 2 || ld <= 24;
+  return work <= 7 * kCus || (local && panels >= 3 && work <= 16 * kCus);
 }
 
 // Row tiles set their own lanes, so they are what the row groups' default

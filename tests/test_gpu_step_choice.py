@@ -178,40 +178,46 @@ def _dofs(graph, b):
     return _csr(sp.kron(graph.to_scipy(), np.eye(b) * 2 + 0.5, format="csr"))
 
 
-# the row groups' default is their tiles where these pay.  Random graphs: at one
-# block of the largest union's LDS per CU one panel of columns alone, at two
-# blocks two panels; a covariance of 190 entries per row (one block per CU): FP64
-# up to two panels, FP32 one; with a few large unions all
+# the row groups' default is their tiles where these pay, by the blocks per CU that
+# the largest union leaves, the rounds of blocks and what neighbouring tiles share.
+# One block (1000 tiles of a random graph, 3.9 rounds per panel; 312 tiles, 1.2; a
+# covariance of 190 entries per row, 4.2), two blocks (2813 tiles, 5.5 rounds per
+# panel; 375 tiles), three, and a few large unions
 @pytest.mark.parametrize("name,npr,prec,vt,product", [
-    ("random_1", 16, "mixed", "fp32", 2), ("random_1", 32, "mixed", "fp32", 2),
-    ("random_1", 33, "mixed", "fp32", 1), ("random_1", 16, "fp64", "fp64", 2),
-    ("random_1", 17, "fp64", "fp64", 1), ("random_1", 30, "mixed", "fp64", 0),
-    ("random_2", 64, "mixed", "fp32", 2), ("random_2", 65, "mixed", "fp32", 2),
-    ("random_25", 64, "mixed", "fp32", 2), ("random_25", 65, "mixed", "fp32", 1),
-    ("random_3", 65, "mixed", "fp32", 2), ("random_16", 30, "mixed", "fp64", 2),
+    ("random_1", 32, "mixed", "fp32", 2), ("random_1", 33, "mixed", "fp32", 1),
+    ("random_1", 96, "mixed", "fp32", 1), ("random_1", 24, "fp64", "fp64", 2),
+    ("random_1", 48, "fp64", "fp64", 2), ("random_1", 49, "fp64", "fp64", 1),
+    ("random_1", 64, "mixed", "fp64", 2), ("random_1", 65, "mixed", "fp64", 0),
+    ("random_1s", 128, "mixed", "fp32", 2), ("random_1s", 128, "fp64", "fp64", 2),
+    ("random_2", 64, "mixed", "fp32", 2), ("random_2", 65, "mixed", "fp32", 1),
+    ("random_2", 33, "fp64", "fp64", 1), ("random_2s", 128, "fp64", "fp64", 2),
+    ("random_3", 128, "mixed", "fp32", 2), ("random_16", 128, "mixed", "fp64", 2),
     ("random_big", 64, "fp64", "fp64", 1), ("random_big", 32, "fp64", "fp64", 2),
-    ("wide", 33, "mixed", "fp32", 1), ("wide", 32, "mixed", "fp32", 2),
-    ("wide", 32, "fp64", "fp64", 2), ("wide", 33, "fp64", "fp64", 1),
-    ("wide", 64, "mixed", "fp64", 2), ("hub", 64, "mixed", "fp32", 2),
+    ("wide", 32, "mixed", "fp32", 2), ("wide", 33, "mixed", "fp32", 1),
+    ("wide", 96, "mixed", "fp32", 2), ("wide", 128, "mixed", "fp32", 1),
+    ("wide", 48, "fp64", "fp64", 2), ("wide", 49, "fp64", "fp64", 1),
+    ("wide", 128, "mixed", "fp64", 2), ("hub", 64, "mixed", "fp32", 2),
     ("hub", 64, "fp64", "fp64", 2),
 ])
 def test_tiles_where_they_pay(L, ctx, name, npr, prec, vt, product):
     def hub():
-        a = W.wendland(20000, 48.0, NUG, seed=1).to_scipy().tolil()
-        cols = np.arange(0, 20000, 25)
+        a = W.wendland(100000, 48.0, NUG, seed=1).to_scipy().tolil()
+        cols = np.arange(0, 100000, 125)
         a[7000, cols] = a[7000, cols].toarray() + 1e-4
         a[cols, 7000] = a[cols, 7000].toarray() + 1e-4
         return _csr(a)
-    a = {"random_1": lambda: _dofs(W.er_laplacian(6000, 6000 * 5, seed=1), 4),
-         "random_2": lambda: _dofs(W.er_laplacian(6000, 6000 * 2, seed=1), 4),
-         "random_25": lambda: _dofs(W.er_laplacian(6000, 6000 * 5 // 2, seed=1), 4),
+    a = {"random_1": lambda: _dofs(W.er_laplacian(16000, 16000 * 5, seed=1), 4),
+         "random_1s": lambda: _dofs(W.er_laplacian(5000, 5000 * 5, seed=1), 4),
+         "random_2": lambda: _dofs(W.er_laplacian(45000, 45000 * 5 // 2, seed=1), 4),
+         "random_2s": lambda: _dofs(W.er_laplacian(6000, 6000 * 5 // 2, seed=1), 4),
          "random_3": lambda: _dofs(W.er_laplacian(6000, 6000 * 1, seed=1), 4),
          "random_16": lambda: _dofs(W.er_laplacian(2000, 2000 * 3, seed=1), 16),
          "random_big": lambda: _dofs(W.er_laplacian(140000, 140000, seed=1), 4),
-         "wide": lambda: W.wendland_grid(100, 120, 8.0, nugget=NUG), "hub": hub}[name]()
+         "wide": lambda: W.wendland_grid(230, 300, 8.0, nugget=NUG), "hub": hub}[name]()
     got = _paths(L, ctx, a, npr, prec, vt, lo=1e-2)
     print(f"  {got}", flush=True)
-    blocks = {"random_1": 1, "random_16": 1, "random_25": 2, "wide": 1, "hub": 1}.get(name, 3)
+    blocks = {"random_1": 1, "random_1s": 1, "random_16": 1, "random_2": 2, "random_2s": 2,
+              "wide": 1, "hub": 1}.get(name, 3)
     rows = {1: (633, 1248), 2: (413, 632), 3: (1, 412)}[blocks]  # of 128 bytes in 52.5 and 80 KB
     assert rows[0] <= got["tile_union"] <= rows[1] and got["product"] == product
 
