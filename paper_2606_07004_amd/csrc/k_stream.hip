@@ -1416,17 +1416,22 @@ static bool spmm_item_ok(const SpmmItem& it) {
 
 // One chunk per lane and at most two chunks of rows per resident block of 6
 // per CU: the latency instance (the rule depends on the item alone, so a request
-// takes the same instance in every batch).  From 4 lanes per row on: its four
-// gathers in flight are four of the entries that the row's lanes hold, and on
-// fewer lanes it only added its registers (1 and 2 lanes, 3000 to 40 000 rows
-// of 9 to 50 entries: 1.02 to 1.07 of the estimate's time).  Not with FP16
-// vectors, whose instance spills (3000 to 190 000 rows of 5 to 7 entries, 12 to
-// 96 probes: 0.98 of the time without it, 1.04 with it just past one chunk per
-// block).  Instances of 4 blocks per CU (FP64 values on FP32 vectors, two fused
-// products) take it as far: 0.82 to 0.98 at 1400 to 3070 chunks.
+// takes the same instance in every batch).  Its four gathers in flight are four
+// of the entries that the row's lanes hold: on one or two lanes they never fill,
+// and on up to two blocks per CU it only added its registers (3000 to 40 000 rows
+// of 9 to 50 entries: 1.02 to 1.07 of the estimate's time); with more, and in two
+// even rounds above all, it still pays (150 000 rows of 17 entries, 4 to 8 columns
+// 0.98 to 1.00, 255 000 to 600 000 rows 0.72 to 0.99).  With FP16 vectors it
+// spills, and the plain instance has 8 blocks per CU: only past those 2048 blocks
+// (100 000 rows of 5 to 9 entries in one round 1.02 to 1.08, 150 000 to 600 000
+// rows in two 0.80 to 1.01).  Instances of 4 blocks per CU (FP64 values on FP32
+// vectors, two fused products) take it as far as the others: 0.82 to 0.98 at 1400
+// to 3070 chunks.
 static bool spmm_few(const SpmmItem& it) {
-  return it.g.C == 1 && it.g.L >= 4 && it.g.xbytes >= 4 && it.g.lges == 0 && !it.g.rg &&
-         (it.g.n + rows_per_block(it.g.L) - 1) / rows_per_block(it.g.L) <= 2 * 6 * 256;
+  if (it.g.C != 1 || it.g.lges != 0 || it.g.rg) return false;
+  const int64_t nchunk = (it.g.n + rows_per_block(it.g.L) - 1) / rows_per_block(it.g.L);
+  return nchunk <= 2 * 6 * 256 &&
+         (it.g.xbytes == 2 ? nchunk > 8 * 256 : it.g.L >= 3 || nchunk > 2 * 256);
 }
 
 // Bands of the matrix's frequent stride, from 8 chunks per band (below, the
@@ -1505,9 +1510,8 @@ static hipError_t spmm_launch_c(hipStream_t st, int C, SpmmItem* items, const in
     if (C == 2) return spmm_launch<VT, XT, 2, NF, true>(st, items, idx, cnt);
     return hipErrorInvalidValue;
   }
-  if constexpr (sizeof(XT) >= 4)
-    if (spmm_few(items[idx[0]]))
-      return spmm_launch<VT, XT, 1, NF, false, true>(st, items, idx, cnt);
+  if (spmm_few(items[idx[0]]))
+    return spmm_launch<VT, XT, 1, NF, false, true>(st, items, idx, cnt);
   LD_DISPATCH_C(C, { e = spmm_launch<VT, XT, CC, NF, false>(st, items, idx, cnt); });
   return e;
 }

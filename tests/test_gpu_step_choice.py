@@ -84,6 +84,10 @@ def test_products(L, ctx):
     (20000, 16, "mixed", "fp32", 2, 1), (20000, 8, "mixed", "fp32", 2, 0),
     (20000, 4, "mixed", "fp64", 2, 0), (20000, 4, "fp64", "fp64", 2, 0),
     (20000, 8, "fp64", "fp64", 2, 1), (20000, 64, "half", "fp32", 2, 0),
+    (20000, 12, "mixed", "fp32", 2, 1), (256 * 512, 4, "mixed", "fp32", 2, 0),
+    (256 * 512 + 1, 4, "mixed", "fp32", 2, 1), (128 * 512 + 1, 4, "fp64", "fp64", 2, 1),
+    (64 * 2048, 30, "half", "fp32", 2, 0), (64 * 2048 + 1, 30, "half", "fp32", 2, 1),
+    (64 * 3072 + 1, 30, "half", "fp32", 2, 0),
 ])
 def test_latency_instance(L, ctx, n, npr, prec, vt, k, latency):
     got = _paths(L, ctx, _stripes(n, (1, 37)), npr, prec, vt, k)
@@ -254,6 +258,7 @@ def test_bands_of_whole_runs(L, ctx, n, strides, npr, prec, bands):
     (64 * 1024 + 1, 30, "half", "fp32", 2), (16 * 3072 + 1, 30, "fp64", "fp64", 10),
     (16 * 3072, 30, "fp64", "fp64", 10), (32 * 3072, 30, "mixed", "fp64", 2),
     (20011, 8, "mixed", "fp64", 2), (20011, 60, "half", "fp32", 2),
+    (128 * 512 + 1, 8, "mixed", "fp32", 2), (64 * 2048 + 1, 30, "half", "fp32", 2),
 ])
 def test_values_where_rules_change(L, ctx, n, npr, prec, vt, k):
     a = _stripes(n, (1, 37))
