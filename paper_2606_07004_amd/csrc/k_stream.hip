@@ -1421,17 +1421,27 @@ static bool spmm_item_ok(const SpmmItem& it) {
 // and on up to two blocks per CU it only added its registers (3000 to 40 000 rows
 // of 9 to 50 entries: 1.02 to 1.07 of the estimate's time); with more, and in two
 // even rounds above all, it still pays (150 000 rows of 17 entries, 4 to 8 columns
-// 0.98 to 1.00, 255 000 to 600 000 rows 0.72 to 0.99).  With FP16 vectors it
-// spills, and the plain instance has 8 blocks per CU: only past those 2048 blocks
-// (100 000 rows of 5 to 9 entries in one round 1.02 to 1.08, 150 000 to 600 000
-// rows in two 0.80 to 1.01).  Instances of 4 blocks per CU (FP64 values on FP32
-// vectors, two fused products) take it as far as the others: 0.82 to 0.98 at 1400
-// to 3070 chunks.
+// 0.98 to 1.00, 255 000 to 600 000 rows 0.72 to 0.99).
+// FP16 vectors: the plain instance has 8 blocks per CU and this one, which spills,
+// 6, so only past one round of the former (100 000 rows of 5 to 9 entries within it
+// 1.02 to 1.08, 150 000 to 600 000 rows in two 0.80 to 1.01).  With FP64 values
+// they have 6 and 4: past one round of the former up to two of this one's, 5% more
+// counted in, which add little (8 to 124 probes, rows of 4 to 48 entries: 1545 to
+// 1600 chunks 0.94 to 1.11, 1640 and 1680 chunks 0.82 to 1.04, 1875 chunks 0.85 to
+// 0.95, 2100 chunks 0.88 to 1.01, 2300 to 3000 chunks 0.93 to 1.08).  Also on 8 lanes and
+// more up to 640 chunks, where few waves are resident in either: 64 and 124 probes
+// on 1000 to 20 000 rows of 17 to 48 entries 0.93 to 1.02, of 6 entries up to 1.03.
+// Other instances of 4 blocks per CU (FP64 values on FP32 vectors, two fused
+// products) take it as far as the rest: 0.82 to 0.98 at 1400 to 3070 chunks.
 static bool spmm_few(const SpmmItem& it) {
   if (it.g.C != 1 || it.g.lges != 0 || it.g.rg) return false;
   const int64_t nchunk = (it.g.n + rows_per_block(it.g.L) - 1) / rows_per_block(it.g.L);
-  return nchunk <= 2 * 6 * 256 &&
-         (it.g.xbytes == 2 ? nchunk > 8 * 256 : it.g.L >= 3 || nchunk > 2 * 256);
+  if (nchunk > 2 * 6 * 256) return false;
+  if (it.g.xbytes == 2)
+    return (it.g.L >= 8 && nchunk <= 640) ||
+           (it.vt == VT_F64 ? 20 * nchunk > 21 * 6 * 256 && 20 * nchunk <= 21 * 2 * 4 * 256
+                             : nchunk > 8 * 256);
+  return it.g.L >= 3 || nchunk > 2 * 256;
 }
 
 // Bands of the matrix's frequent stride, from 8 chunks per band (below, the

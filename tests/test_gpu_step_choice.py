@@ -83,11 +83,15 @@ def test_products(L, ctx):
     (32 * 3072, 30, "mixed", "fp64", 2, 1), (16 * 3072, 30, "fp64", "fp64", 10, 1),
     (20000, 16, "mixed", "fp32", 2, 1), (20000, 8, "mixed", "fp32", 2, 0),
     (20000, 4, "mixed", "fp64", 2, 0), (20000, 4, "fp64", "fp64", 2, 0),
-    (20000, 8, "fp64", "fp64", 2, 1), (20000, 64, "half", "fp32", 2, 0),
+    (20000, 8, "fp64", "fp64", 2, 1), (20000, 64, "half", "fp32", 2, 1),
     (20000, 12, "mixed", "fp32", 2, 1), (256 * 512, 4, "mixed", "fp32", 2, 0),
     (256 * 512 + 1, 4, "mixed", "fp32", 2, 1), (128 * 512 + 1, 4, "fp64", "fp64", 2, 1),
     (64 * 2048, 30, "half", "fp32", 2, 0), (64 * 2048 + 1, 30, "half", "fp32", 2, 1),
-    (64 * 3072 + 1, 30, "half", "fp32", 2, 0),
+    (64 * 3072 + 1, 30, "half", "fp32", 2, 0), (32 * 640, 64, "half", "fp32", 2, 1),
+    (32 * 640 + 1, 64, "half", "fp32", 2, 0), (16 * 640, 124, "half", "fp64", 2, 1),
+    (64 * 640, 30, "half", "fp64", 2, 0), (32 * 1612, 64, "half", "fp64", 2, 0),
+    (32 * 1612 + 1, 64, "half", "fp64", 2, 1), (32 * 2150, 64, "half", "fp64", 2, 1),
+    (32 * 2150 + 1, 64, "half", "fp64", 2, 0),
 ])
 def test_latency_instance(L, ctx, n, npr, prec, vt, k, latency):
     got = _paths(L, ctx, _stripes(n, (1, 37)), npr, prec, vt, k)
@@ -259,6 +263,7 @@ def test_bands_of_whole_runs(L, ctx, n, strides, npr, prec, bands):
     (16 * 3072, 30, "fp64", "fp64", 10), (32 * 3072, 30, "mixed", "fp64", 2),
     (20011, 8, "mixed", "fp64", 2), (20011, 60, "half", "fp32", 2),
     (128 * 512 + 1, 8, "mixed", "fp32", 2), (64 * 2048 + 1, 30, "half", "fp32", 2),
+    (32 * 1612 + 1, 64, "half", "fp64", 2), (16 * 640, 124, "half", "fp32", 2),
 ])
 def test_values_where_rules_change(L, ctx, n, npr, prec, vt, k):
     a = _stripes(n, (1, 37))
