@@ -1678,17 +1678,20 @@ static int update_nv_class(int nv) { return nv <= 1 ? 1 : (nv == 2 ? 2 : (nv <= 
 // four vectors with one chunk per lane: windows 3 and 4 on 350^2 and 507^2
 // rows, 30 and 64 FP32 probes, 0.96 to 0.99 of the time per estimate, FP64 0.97
 // to 1.00; FP64 at 20 rounds (800^2 rows, 30 probes) 1.01, hence 12.
-// Rows of less than a 128-byte line (one vector; two to four: of 4 columns) only
-// up to 320 chunks of rows, where the coefficients' latency is most of the time:
+// Rows of less than a 128-byte line (one vector) only up to 320 chunks of rows,
+// where the coefficients' latency is most of the time:
 // 3000 and 10 000 rows of 2 to 16 probes 0.98 to 0.99 of the estimate's time,
 // but 100 000 to 1e6 rows 1.01 to 1.02 (400 000 rows, 4 FP32 probes: the update
-// 17.6 -> 19.3 us).  FP16 rows again past their 1024 resident blocks (0.95).
+// 17.6 -> 19.3 us).  FP16 rows again past their 1024 resident blocks (0.95).  Two to
+// four vectors of 4 columns: up to 1000 chunks 0.97 to 1.00 of the estimate's time,
+// from 1500 to 4700 1.00 to 1.02 with FP64 vectors or two FP32 ones (7800: 0.99 to
+// 1.00), three or four FP32 ones 0.98.
 static bool update_pre(const UpdateItem& it) {
   if (it.nv > 4 || it.v1) return false;
   const int64_t nchunk = (it.g.n + rows_per_block(it.g.L) - 1) / rows_per_block(it.g.L);
-  if ((it.nv > 1 ? it.g.ld <= 4 : it.g.ncolv < 8) && nchunk > 320 &&
-      !(it.g.xbytes == 2 && nchunk > 1024))
+  if (it.nv == 1 && it.g.ncolv < 8 && nchunk > 320 && !(it.g.xbytes == 2 && nchunk > 1024))
     return false;
+  if (it.nv > 1 && it.g.ld <= 4 && nchunk > 1024 && (it.nv == 2 || it.g.xbytes == 8)) return false;
   if (it.nv > 1)
     return it.g.C == 1 && it.g.xbytes >= 4 &&
            nchunk <= (it.g.xbytes == 8 ? 12 : 24) * (int64_t)kMaxBlocks;

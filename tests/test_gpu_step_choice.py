@@ -99,13 +99,16 @@ def test_latency_instance(L, ctx, n, npr, prec, vt, k, latency):
 
 
 # the update that reads a row ahead: rows of less than a line (7 chunks and
-# fewer) up to 320 chunks of rows, FP16 ones past 1024 again; wider rows up to 24
+# fewer) up to 320 chunks of rows, FP16 ones past 1024 again, with two to four
+# vectors those of 4 columns up to 1024 chunks; wider rows up to 24
 # (12) rounds of 2048 chunks
 @pytest.mark.parametrize("n,npr,prec,k,ahead", [
     (256 * 320, 4, "mixed", 2, 1), (256 * 320 + 1, 4, "mixed", 2, 0),
     (32 * 320, 28, "mixed", 2, 1), (32 * 320 + 1, 28, "mixed", 2, 0),
     (32 * 320 + 1, 30, "mixed", 2, 1), (256 * 320 + 1, 2, "fp64", 2, 0),
-    (128 * 320, 4, "fp64", 3, 1), (128 * 320 + 1, 4, "fp64", 3, 0), (64 * 320 + 1, 8, "fp64", 3, 1),
+    (128 * 1024, 4, "fp64", 4, 1), (128 * 1024 + 1, 4, "fp64", 4, 0),
+    (256 * 1024, 4, "mixed", 3, 1), (256 * 1024 + 1, 4, "mixed", 3, 0),
+    (256 * 1024 + 1, 4, "mixed", 4, 1), (64 * 1024 + 1, 8, "fp64", 4, 1),
     (64 * 320 + 1, 30, "half", 2, 0), (64 * 1024 + 1, 30, "half", 2, 1),
     (16 * 24 * 2048, 64, "mixed", 2, 1), (16 * 24 * 2048 + 1, 64, "mixed", 2, 0),
     (16 * 12 * 2048, 30, "fp64", 4, 1), (16 * 12 * 2048 + 1, 30, "fp64", 4, 0),
